@@ -207,9 +207,10 @@ int ecspmv_run_batch(const ecspmv_matrix *const *As, const void *const *d_xs, vo
  * with N = nb in {1, 2, 4, 8}; the paper leaves small N > 1 as future work, Section 10).  d_X: device, n rows of nb
  * FP16 (row-major: the nb values that belong to one column of W are adjacent), d_Y: device, m rows of nb FP16; every
  * entry of Y is written.  The deltas are decoded once and every stored entry of W is read once for all nb products.
- * One kernel launch, asynchronous on `stream`, no allocation.  nb = 1 is ecspmv_run.  Where 2*n*nb bytes of X plus
- * 4*nb bytes per partial sum do not fit the LDS of a compute unit, the call runs as 2 or 4 launches of nb/2 or nb/4
- * right-hand sides each (same X, Y and results; the image is then read once per launch).
+ * One kernel launch, asynchronous on `stream`, no allocation.  nb = 1 is ecspmv_run.  Where the 2*n*nb bytes of X do not
+ * fit the LDS of a compute unit, the launch has 2 or 4 workgroups per panel with nb/2 or nb/4 right-hand sides each;
+ * where X fits but not 4*nb bytes per partial sum beside it, the partial sums are added up in several phases (same
+ * results either way).
  * For a matrix built with ecspmv_build_*_f32, X and Y are FP32 (and 4*n*nb bytes of X count for LDS).
  * ECSPMV_ERR_UNSUPPORTED if the image holds a 16-grained block set, or an 8-grained one with FP32 values (the default
  * build options produce neither), or if not even two right-hand sides fit LDS; ECSPMV_ERR_INVALID for other nb. */

@@ -378,38 +378,42 @@ int ecspmv_run_multi(const ecspmv_matrix *A, const void *d_X, void *d_Y, int32_t
     int lim = 0;
     int e = lds_limit(&lim);
     if (e) return hip_status(e);
-    // All nb right-hand sides in one launch if X and the partial sums fit LDS; otherwise several launches of nb / 2
-    // or nb / 4 right-hand sides each, which read their columns of X and write their columns of Y with the row
-    // stride nb (the image is then read once per launch).
-    uint32_t per = (uint32_t)nb, x_bytes = 0;
-    uint64_t lds = 0;
+    const uint32_t threads = im.threads_per_wg ? (uint32_t)im.threads_per_wg : 1024u, waves = threads / 64u;
+    // `per` columns of X and their partial sums sit in the LDS of a workgroup, so a panel takes nb / per workgroups, all
+    // of one launch.  Where the partial sums of a whole panel do not fit beside X, the residual chunks are taken in
+    // phases of k chunks per wavefront, and the partial sums of a phase are added up before the next one.
+    auto x_bytes_of = [&](uint32_t per) -> uint64_t { return ((uint64_t)im.n * vw * per + 15u) / 16u * 16u; };
+    auto lds_of = [&](uint32_t per, uint32_t k) -> uint64_t {           // k = 0: one phase
+        const uint64_t fixed = x_bytes_of(per) + im.meta_stride;
+        if (k == 0) return fixed + ((uint64_t)im.max_slots * 4u * per + 15u) / 16u * 16u;
+        return fixed + 2u * 16u * 4u * per + ((uint64_t)im.max_block_slots + 64u * waves * k) * 4u * per;
+    };
+    if (lds_of(2, 0) > (uint64_t)lim) return ECSPMV_ERR_UNSUPPORTED;    // not even two right-hand sides fit
+    uint32_t per = (uint32_t)nb, k = 0;
     for (;; per /= 2) {
-        x_bytes = ((uint32_t)im.n * vw * per + 15u) / 16u * 16u;
-        const uint32_t slot_bytes = (im.max_slots * 4u * per + 15u) / 16u * 16u;
-        lds = (uint64_t)x_bytes + im.meta_stride + slot_bytes;
-        if (lds <= (uint64_t)lim) break;
-        if (per == 2) return ECSPMV_ERR_UNSUPPORTED;                  // not even two right-hand sides fit
+        k = 0;
+        if (lds_of(per, 0) <= (uint64_t)lim) break;
+        if (lds_of(per, 1) > (uint64_t)lim) continue;                  // (with per = 2 one phase always fits)
+        const uint32_t want = (im.max_chunks + waves - 1u) / waves;    // chunks of a wavefront
+        for (k = 1; k < want && lds_of(per, k + 1u) <= (uint64_t)lim; ++k) {}
+        break;
     }
-    const uint32_t threads = im.threads_per_wg ? (uint32_t)im.threads_per_wg : 1024u;
-    for (uint32_t c0 = 0; c0 < (uint32_t)nb; c0 += per) {
-        ecs::EcsBatch b;
-        std::memset(&b, 0, sizeof(b));
-        b.count = 1;
-        ecs::EcsBatchItem &it = b.item[0];
-        it.image = static_cast<const uint8_t *>(A->d_image);
-        it.x = reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(d_X) + (size_t)c0 * vw);
-        it.y = reinterpret_cast<uint16_t *>(static_cast<uint8_t *>(d_Y) + (size_t)c0 * vw);
-        it.n = (uint32_t)im.n;
-        it.panel_stride = im.panel_stride;
-        it.meta_stride = im.meta_stride;
-        it.x_bytes = x_bytes;
-        it.block_end = (uint32_t)im.num_panels;
-        it.row_stride = (uint32_t)nb;                                 // of X and Y, in elements
-        int s = hip_status(ecs::launch_ecspmv_multi(b, threads, (uint32_t)lds, im.type_mask, (uint32_t)im.delta_bits,
-                                                    (uint32_t)im.value_bits, per, stream));
-        if (s) return s;
-    }
-    return ECSPMV_OK;
+    ecs::EcsBatch b;
+    std::memset(&b, 0, sizeof(b));
+    b.count = 1;
+    b.per_phase = k;
+    ecs::EcsBatchItem &it = b.item[0];
+    it.image = static_cast<const uint8_t *>(A->d_image);
+    it.x = static_cast<const uint16_t *>(d_X);
+    it.y = static_cast<uint16_t *>(d_Y);
+    it.n = (uint32_t)im.n;
+    it.panel_stride = im.panel_stride;
+    it.meta_stride = im.meta_stride;
+    it.x_bytes = (uint32_t)x_bytes_of(per);
+    it.block_end = (uint32_t)im.num_panels;
+    it.row_stride = (uint32_t)nb;                                       // of X and Y, in elements
+    return hip_status(ecs::launch_ecspmv_multi(b, threads, (uint32_t)lds_of(per, k), im.type_mask, (uint32_t)im.delta_bits,
+                                               (uint32_t)im.value_bits, per, stream));
 }
 
 int ecspmv_csr_build_dense(const uint16_t *W, int64_t m, int64_t n, int64_t ld, ecspmv_csr **out)

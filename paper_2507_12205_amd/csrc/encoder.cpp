@@ -811,12 +811,15 @@ int build_image(const Csr &A, const BuildParams &bp, Image &out)
         max_g = 1 << top;                                                    // halved by the loop: drops set `top`
     }
     uint32_t stride = 256, meta = 16, slots = 1;
+    out.max_block_slots = out.max_chunks = 0;
     for (auto &im : imgs) {
         if (im.err) return im.err;
         if (im.bytes.size() > 0xFFFFF000ull) return -2;                      // offsets inside a panel are 32-bit
         stride = std::max<uint32_t>(stride, (uint32_t)im.bytes.size());
         meta = std::max(meta, im.meta_bytes);
         slots = std::max(slots, im.lds_slots);
+        out.max_block_slots = std::max(out.max_block_slots, im.nslots);
+        out.max_chunks = std::max(out.max_chunks, (im.lds_slots - im.nslots) / ECS_CHUNK_LANES);
     }
     meta = align_up(meta, 16);
     // 4 KB of zeros after the last panel: loads that stand in for missing chunks may run past a short last panel

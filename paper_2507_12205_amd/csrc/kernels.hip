@@ -115,41 +115,62 @@ __device__ __forceinline__ float fma_h(uint32_t w_bits, float xf, float acc)
     return fmaf(half_bits_to_float(w_bits), xf, acc);
 }
 
-// the NB right-hand sides of one column sit side by side in LDS (x[col * NB + b]): one LDS read fetches them all
+// The values of x at one column as they sit in LDS, side by side (x[col * NB + b]): one read fetches up to 16 bytes of them
 template <int NB, int VW>
-__device__ __forceinline__ void gather_x(const uint16_t *xs, uint32_t col, float (&xv)[NB])
-{
-    if constexpr (VW == 4) {
-        const float *xf = reinterpret_cast<const float *>(xs);
-        if constexpr (NB == 1) {
-            xv[0] = xf[col];
-        } else if constexpr (NB == 2) {
-            const float2 w = *reinterpret_cast<const float2 *>(xf + 2u * col);
-            xv[0] = w.x, xv[1] = w.y;
+struct XWords {
+    uint32_t w[NB * VW <= 4 ? 1 : NB * VW / 4];
+    __device__ __forceinline__ void read(const uint16_t *xs, uint32_t col)
+    {
+        const uint8_t *p = reinterpret_cast<const uint8_t *>(xs) + col * (NB * VW);
+        if constexpr (NB * VW == 2) {
+            w[0] = *reinterpret_cast<const uint16_t *>(p);
+        } else if constexpr (NB * VW == 4) {
+            w[0] = *reinterpret_cast<const uint32_t *>(p);
+        } else if constexpr (NB * VW == 8) {
+            const uint2 t = *reinterpret_cast<const uint2 *>(p);
+            w[0] = t.x, w[1] = t.y;
         } else {
 #pragma unroll
-            for (int q = 0; q < NB / 4; ++q) {
-                const float4 w = *reinterpret_cast<const float4 *>(xf + NB * col + 4 * q);
-                xv[4 * q] = w.x, xv[4 * q + 1] = w.y, xv[4 * q + 2] = w.z, xv[4 * q + 3] = w.w;
+            for (int q = 0; q < NB * VW / 16; ++q) {
+                const uint4 t = reinterpret_cast<const uint4 *>(p)[q];
+                w[4 * q] = t.x, w[4 * q + 1] = t.y, w[4 * q + 2] = t.z, w[4 * q + 3] = t.w;
             }
         }
-    } else if constexpr (NB == 1) {
-        xv[0] = half_bits_to_float(xs[col]);
-    } else if constexpr (NB == 2) {
-        const uint32_t w = *reinterpret_cast<const uint32_t *>(xs + 2u * col);
-        xv[0] = half_bits_to_float(w & 0xFFFF), xv[1] = half_bits_to_float(w >> 16);
-    } else if constexpr (NB == 4) {
-        const uint2 w = *reinterpret_cast<const uint2 *>(xs + 4u * col);
-        xv[0] = half_bits_to_float(w.x & 0xFFFF), xv[1] = half_bits_to_float(w.x >> 16);
-        xv[2] = half_bits_to_float(w.y & 0xFFFF), xv[3] = half_bits_to_float(w.y >> 16);
-    } else {
-        const uint4 w = *reinterpret_cast<const uint4 *>(xs + 8u * col);
-        xv[0] = half_bits_to_float(w.x & 0xFFFF), xv[1] = half_bits_to_float(w.x >> 16);
-        xv[2] = half_bits_to_float(w.y & 0xFFFF), xv[3] = half_bits_to_float(w.y >> 16);
-        xv[4] = half_bits_to_float(w.z & 0xFFFF), xv[5] = half_bits_to_float(w.z >> 16);
-        xv[6] = half_bits_to_float(w.w & 0xFFFF), xv[7] = half_bits_to_float(w.w >> 16);
     }
-}
+    __device__ __forceinline__ float get(int b) const
+    {
+        if constexpr (VW == 4) return __uint_as_float(w[b]);
+        return half_bits_to_float((b & 1) ? w[b >> 1] >> 16 : w[b >> 1] & 0xFFFFu);
+    }
+};
+
+// Several right-hand sides: the NB partial sums of a slot or lane unit lie in LDS in groups of up to four side by side,
+// the groups `pstride` slots apart (groups of eight would put a wavefront's stores 32 bytes apart: 20 % of the whole launch
+// with eight right-hand sides).
+template <int NB>
+struct Partial {
+    static constexpr int G = NB < 4 ? NB : 4;
+    typedef float vec __attribute__((ext_vector_type(G)));
+    static __device__ __forceinline__ void put(float *base, uint32_t pstride, uint32_t slot, const float (&v)[NB])
+    {
+#pragma unroll
+        for (int p = 0; p < NB / G; ++p) {
+            vec t;
+#pragma unroll
+            for (int k = 0; k < G; ++k) t[k] = v[p * G + k];
+            reinterpret_cast<vec *>(base)[slot + p * pstride] = t;
+        }
+    }
+    static __device__ __forceinline__ void add(const float *base, uint32_t pstride, uint32_t slot, float (&v)[NB])
+    {
+#pragma unroll
+        for (int p = 0; p < NB / G; ++p) {
+            const vec t = reinterpret_cast<const vec *>(base)[slot + p * pstride];
+#pragma unroll
+            for (int k = 0; k < G; ++k) v[p * G + k] += t[k];
+        }
+    }
+};
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -191,6 +212,7 @@ struct Ctx {
     const uint16_t *xs;        // LDS: x as FP16 bits
     const uint8_t *meta;       // LDS copy of the panel's meta region
     float *slots;              // LDS partial sums
+    uint32_t pstride;          // several right-hand sides: see Partial
     uint32_t wave, lane, nwaves;
     uint32_t wshift;           // log2(nwaves) if the workgroup has a power-of-two number of wavefronts, else 32
     // quotient and remainder by the number of wavefronts: shifts in the usual case (a division by a run-time value is
@@ -257,9 +279,9 @@ __device__ __forceinline__ void compute_unit(const Ctx &c, const uint16_t *utab,
         const int incl = row16_incl_scan((int)rel[3]);
         start = (uint32_t)ue[0] + (uint32_t)incl - rel[3];
     }
-    float xv[4][NB];
+    XWords<NB, VW> xv[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) gather_x<NB, VW>(c.xs, start + rel[k], xv[k]);
+    for (int k = 0; k < 4; ++k) xv[k].read(c.xs, start + rel[k]);
     float acc[G][NB];
 #pragma unroll
     for (int q = 0; q < G; ++q)
@@ -272,22 +294,29 @@ __device__ __forceinline__ void compute_unit(const Ctx &c, const uint16_t *utab,
             const uint32_t word = ((f >> 1) & 3) == 0 ? q.x : ((f >> 1) & 3) == 1 ? q.y : ((f >> 1) & 3) == 2 ? q.z : q.w;
             const uint32_t hb = (f & 1) ? (word >> 16) : (word & 0xFFFF);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) acc[f % G][b] = fma_h(hb, xv[f / G][b], acc[f % G][b]);
+            for (int b = 0; b < NB; ++b) acc[f % G][b] = fma_h(hb, xv[f / G].get(b), acc[f % G][b]);
         } else {
             const uint4 q = r.v[f >> 2];
             const uint32_t word = (f & 3) == 0 ? q.x : (f & 3) == 1 ? q.y : (f & 3) == 2 ? q.z : q.w;
 #pragma unroll
-            for (int b = 0; b < NB; ++b) acc[f % G][b] = fmaf(__uint_as_float(word), xv[f / G][b], acc[f % G][b]);
+            for (int b = 0; b < NB; ++b) acc[f % G][b] = fmaf(__uint_as_float(word), xv[f / G].get(b), acc[f % G][b]);
         }
     }
+    typedef Partial<NB> P;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
+    for (int p = 0; p < NB / P::G; ++p) {
+        typename P::vec t;
 #pragma unroll
-        for (int q = 0; q < G; ++q) acc[q][b] = row16_allreduce(acc[q][b]);
-        float out = acc[0][b];
+        for (int k = 0; k < P::G; ++k) {
+            const int b = p * P::G + k;
 #pragma unroll
-        for (int q = 1; q < G; ++q) out = (j == (uint32_t)q) ? acc[q][b] : out;
-        if (active && j < (uint32_t)G) c.slots[(uint32_t)ue[1 + j] * NB + b] = out;
+            for (int q = 0; q < G; ++q) acc[q][b] = row16_allreduce(acc[q][b]);
+            float out = acc[0][b];
+#pragma unroll
+            for (int q = 1; q < G; ++q) out = (j == (uint32_t)q) ? acc[q][b] : out;
+            t[k] = out;
+        }
+        if (active && j < (uint32_t)G) reinterpret_cast<typename P::vec *>(c.slots)[ue[1 + j] + p * c.pstride] = t;
     }
 }
 
@@ -414,9 +443,10 @@ __device__ __forceinline__ void load_chunk(const Ctx &c, uint32_t res_off, uint3
 
 // One partial sum per lane unit goes to LDS (`part`, indexed by the lane unit's position in the residual stream); a
 // row's lane units are consecutive, so the final pass adds a range of them.  No cross-lane reduction is needed here.
+// `pch`: the chunk's place in `part`.
 template <int DB, bool FENCE, int NB, int VW>
 __device__ __forceinline__ void compute_chunk(const Ctx &c, const EcsRChunk *rch, const EcsREntry *ren, float *part,
-                                              uint32_t ch, const ChunkRegs<DB, VW> &r)
+                                              uint32_t ch, uint32_t pch, const ChunkRegs<DB, VW> &r)
 {
     if constexpr (DB == 4 && NB == 1 && VW == 2) {
         // 4-bit deltas, FP16, one right-hand side: the 16 prefix sums of a lane are made eight at a time inside 32-bit
@@ -455,7 +485,7 @@ __device__ __forceinline__ void compute_chunk(const Ctx &c, const EcsRChunk *rch
             const uint32_t word = vw[i >> 1];
             acc = fma_h((i & 1) ? (word >> 16) : (word & 0xFFFF), xv, acc);
         }
-        part[64u * ch + c.lane] = acc;
+        part[64u * pch + c.lane] = acc;
         if constexpr (FENCE) __builtin_amdgcn_sched_barrier(0);
         return;
     }
@@ -465,13 +495,29 @@ __device__ __forceinline__ void compute_chunk(const Ctx &c, const EcsRChunk *rch
 #pragma unroll
         for (int i = 0; i < 16; ++i) rel[i] = (r.d[i / 2] >> (16 * (i % 2))) & 0xFFFFu;
     } else {
-        // lane-local inclusive prefix of the 16 deltas
-        constexpr int PER = 32 / DB;                  // deltas per 32-bit word
         uint32_t run = 0;
+        if constexpr (DB == 4) {
+            // as above, not doubled: byte k of a word is the prefix up to nibble 2k + 1 (or 2k), at most 120
+            constexpr uint32_t M = 0x0F0F0F0Fu;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            run += (r.d[i / PER] >> (DB * (i % PER))) & ((1u << DB) - 1u);
-            rel[i] = run;
+            for (int w = 0; w < 2; ++w) {
+                const uint32_t hi = (r.d[w] >> 4) & M;
+                uint32_t t = (r.d[w] & M) + hi;
+                asm("v_lshl_add_u32 %0, %1, 8, %1" : "=v"(t) : "v"(t));
+                asm("v_lshl_add_u32 %0, %1, 16, %1" : "=v"(t) : "v"(t));
+                const uint32_t e = t - hi;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    rel[8 * w + 2 * k] = run + ((e >> (8 * k)) & 0xFFu), rel[8 * w + 2 * k + 1] = run + ((t >> (8 * k)) & 0xFFu);
+                run += t >> 24;
+            }
+        } else {
+            // lane-local inclusive prefix of the 16 deltas
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                run += (r.d[i / 4] >> (8 * (i % 4))) & 0xFFu;
+                rel[i] = run;
+            }
         }
         // wave64 prefix scan of the lane totals; the segment's entry folds base column and earlier lanes
         const int incl = wave64_incl_scan((int)run);
@@ -486,22 +532,27 @@ __device__ __forceinline__ void compute_chunk(const Ctx &c, const EcsRChunk *rch
     uint32_t vw[4 * VW];
 #pragma unroll
     for (int k = 0; k < VW; ++k) vw[4 * k] = r.v[k].x, vw[4 * k + 1] = r.v[k].y, vw[4 * k + 2] = r.v[k].z, vw[4 * k + 3] = r.v[k].w;
+    auto value = [&](int i) -> float {
+        if constexpr (VW == 2) return half_bits_to_float((i & 1) ? (vw[i >> 1] >> 16) : (vw[i >> 1] & 0xFFFFu));
+        else return __uint_as_float(vw[i]);
+    };
+    // several right-hand sides: eight entries' x values on their way at a time (sixteen need more registers and are no
+    // faster, four are 1 % slower with four right-hand sides)
+    constexpr int GB = NB == 1 ? 16 : 8;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        float xv[NB];
-        gather_x<NB, VW>(c.xs, (uint32_t)(start + (int)rel[i]), xv);
-        if constexpr (VW == 2) {
-            const uint32_t word = vw[i >> 1];
-            const uint32_t hb = (i & 1) ? (word >> 16) : (word & 0xFFFF);
+    for (int g = 0; g < 16; g += GB) {
+        XWords<NB, VW> xv[GB];
 #pragma unroll
-            for (int b = 0; b < NB; ++b) acc[b] = fma_h(hb, xv[b], acc[b]);
-        } else {
+        for (int i = 0; i < GB; ++i) xv[i].read(c.xs, (uint32_t)(start + (int)rel[g + i]));
 #pragma unroll
-            for (int b = 0; b < NB; ++b) acc[b] = fmaf(__uint_as_float(vw[i]), xv[b], acc[b]);
-        }
+        for (int i = 0; i < GB; ++i)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[b] = fmaf(value(g + i), xv[i].get(b), acc[b]);
+        if constexpr (GB < 16)                      // these sums before further reads
+#pragma unroll
+            for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(acc[b])::"memory");
     }
-#pragma unroll
-    for (int b = 0; b < NB; ++b) part[(64u * ch + c.lane) * NB + b] = acc[b];
+    Partial<NB>::put(part, c.pstride, 64u * pch + c.lane, acc);
     // Nothing ties one chunk's arithmetic to the next: with two buffers the scheduler would interleave two chunks
     // and need 20 more registers, which costs a workgroup per compute unit where workgroups share one.
     if constexpr (FENCE) __builtin_amdgcn_sched_barrier(0);
@@ -511,6 +562,7 @@ template <int DB, int DEPTH, bool FENCE, int NB, int VW>
 struct ResidualSet {
     ChunkRegs<DB, VW> buf[DEPTH];
     uint32_t nlanes, n, c0, res_off, zero_off;
+    uint32_t part0;            // first chunk of the phase whose partial sums `part` holds (several right-hand sides)
     const EcsRChunk *rch;
     const EcsREntry *ren;
     float *part;
@@ -521,7 +573,8 @@ struct ResidualSet {
         nlanes = hdr[PH_NRLANES];
         res_off = hdr[PH_RD_OFF];
         zero_off = hdr[PH_ZERO_OFF];
-        part = c.slots + hdr[PH_NSLOTS] * NB;
+        part = c.slots + hdr[PH_NSLOTS] * Partial<NB>::G;
+        part0 = 0;
         rch = reinterpret_cast<const EcsRChunk *>(c.meta + hdr[PH_RCHUNK_OFF]);
         ren = reinterpret_cast<const EcsREntry *>(c.meta + hdr[PH_RENTRY_OFF]);
         const uint32_t nch = (nlanes + 63u) >> 6;
@@ -540,8 +593,18 @@ struct ResidualSet {
     {
         if (k < 3) ECS_TRACE_DRAIN(c, 5 + 2 * k);
         if (k < 3) ECS_STAMP(c, 5 + 2 * k);
-        compute_chunk<DB, FENCE, NB, VW>(c, rch, ren, part, chunk_of(c, k), buf[d]);
+        compute_chunk<DB, FENCE, NB, VW>(c, rch, ren, part, chunk_of(c, k), chunk_of(c, k) - (NB > 1 ? part0 : 0u), buf[d]);
         if (k < 3) ECS_STAMP(c, 6 + 2 * k);
+    }
+    // chunks i0 .. i1 - 1 of this wavefront (one buffer): a wavefront's next chunk, be it in the next phase, is on its
+    // way while the rows of this phase are summed
+    __device__ __forceinline__ void run_phase(const Ctx &c, uint32_t i0, uint32_t i1)
+    {
+        static_assert(NB == 1 || DEPTH == 1, "phases are written for one buffer");
+        for (uint32_t i = i0; i < min(i1, n); ++i) {
+            step(c, i, 0);
+            if (i + 1u < n) load_chunk<DB, VW>(c, res_off, zero_off, chunk_of(c, i + 1u), nlanes, buf[0]);
+        }
     }
     __device__ __forceinline__ void run(const Ctx &c)
     {
@@ -616,25 +679,43 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
             it.meta_stride = rd(t.x, a + 2u), it.x_bytes = rd(t.y, a + 2u), it.block_end = rd(t.z, a + 2u);
         }
     }
-    const uint16_t *__restrict__ x = it.x;
-    uint16_t *__restrict__ y = it.y;
     const uint32_t n = it.n * NB * (VW / 2), meta_stride = it.meta_stride, x_bytes = it.x_bytes;   // n: 2-byte units of x
     // several right-hand sides: elements from one row of X (and of Y) to the next.  NB when the launch handles all
     // columns of X; larger when X has more columns than this launch takes.
     uint32_t ld = NB;
+    uint32_t panel_index = blockIdx.x - block0;
     if constexpr (NB > 1) {
-        const uint32_t given = row_stride0;
-        if (given) ld = given;
+        ld = row_stride0;
+        // Several workgroups per panel, each with NB of the columns of X (where not all fit LDS, or where there are few
+        // panels): the workgroups of a panel sit 8 apart in the grid, that is on the same XCD, so that the image
+        // comes from HBM once and from that XCD's L2 for the others.
+        const uint32_t splits = ld / NB, panels = block_end0;
+        if (splits > 1u) {
+            const uint32_t g = panel_index / (8u * splits), r = panel_index % (8u * splits);
+            const uint32_t in_group = min(8u, panels - 8u * g);
+            const uint32_t h = r / in_group;
+            panel_index = 8u * g + r % in_group;
+            it.x += h * (NB * VW / 2), it.y += h * (NB * VW / 2);
+        }
     }
+    const uint16_t *__restrict__ x = it.x;
+    uint16_t *__restrict__ y = it.y;
 
     extern __shared__ uint4 lds4[];
     uint8_t *lds = reinterpret_cast<uint8_t *>(lds4);
     uint16_t *xs = reinterpret_cast<uint16_t *>(lds);
     uint8_t *meta = lds + x_bytes;
     float *slots = reinterpret_cast<float *>(lds + x_bytes + meta_stride);
+    // several right-hand sides: chunks a wavefront takes per phase (the count of matrices is 1), and with more than one
+    // phase the 16 lanes' sums of the row that runs on into the next phase, kept for two phases in turn
+    const uint32_t per_phase = count;
+    float *carry = slots;
+    if constexpr (NB > 1) {
+        if (per_phase) slots += 2 * 16 * NB;
+    }
 
     const uint32_t tid = threadIdx.x, nt = threads;
-    const uint8_t *panel = it.image + ECS_IMAGE_HEADER + (size_t)it.panel_stride * (blockIdx.x - block0);
+    const uint8_t *panel = it.image + ECS_IMAGE_HEADER + (size_t)it.panel_stride * panel_index;
 
     Ctx c;
     c.panel = panel;
@@ -663,19 +744,21 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // earlier, but those wavefronts request their chunks later, and when the chunks are requested is what decides.)
     // buffers per set: deeper where chunks are small and frequent, shallower where registers run out
     constexpr bool wide = (TM & 12) != 0;
-    constexpr bool straight = !BATCH && NB == 1;
+    constexpr bool straight = !BATCH;
     BlockSet<16, DB, 1, NB, VW, straight> b16;
     BlockSet<8, DB, 1, NB, VW, straight> b8;
     BlockSet<4, DB, wide ? 1 : D4, NB, VW, straight> b4;
     BlockSet<2, DB, wide ? 2 : D2, NB, VW, straight> b2;
-    ResidualSet<DB, wide ? 2 : (TM == 0 && BATCH ? DR0B : DR), TM == 0 && BATCH, NB, VW> rs;
+    ResidualSet<DB, (NB > 1) ? 1 : wide ? 2 : (TM == 0 && BATCH ? DR0B : DR), TM == 0 && BATCH, NB, VW> rs;
     // A launch of an image with block sets that shares its compute units with few others requests the residual set's
     // first chunks only after the barrier: a wavefront cannot pass the barrier before its requests are out, with every
     // set requested up front the whole panel is on its way before anything is computed, and the block sets' first
     // chunks are computed while the residual chunk travels (run_first).  Measured: 3-5 % of a lone launch with one
     // block set, 2 % of a step (7 % of a 5120 x 5120 launch) with two, 6 % with three; with many workgroups per
-    // compute unit (MODE 2) requesting everything first is the faster order.
-    constexpr bool residual_late = TM != 0 && !BATCH && NB == 1 && VW == 2;
+    // compute unit (MODE 2) requesting everything first is the faster order.  Several right-hand sides the same (4 % of a
+    // launch with two on 4096 x 11008 at 8 bits); there it also keeps the kernels for two right-hand sides at 62 instead
+    // of 69 VGPRs, so that two workgroups share a compute unit where their LDS allows it.
+    constexpr bool residual_late = TM != 0 && !BATCH && (VW == 2 || NB > 1);
     const uint4 *p4 = reinterpret_cast<const uint4 *>(panel);
     const uint32_t nmeta = meta_stride / 16u;
     const uint32_t nvec = n / 8u;
@@ -713,6 +796,11 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
         hdr[w] = (uint32_t)__builtin_amdgcn_readlane((int)part, w >> 2);
     }
 
+    if constexpr (NB > 1) {
+        const uint32_t chunks = per_phase ? per_phase * c.nwaves : (hdr[PH_NRLANES] + 63u) >> 6;      // of a phase
+        c.pstride = hdr[PH_NSLOTS] + 64u * chunks;
+    }
+
     // As soon as the header is here, the first chunks of every set are requested (one per register buffer), before
     // anything is computed and before the tables and x have even reached LDS.
     uint32_t dealt = 0;
@@ -732,35 +820,58 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // tables and x into LDS
     // (no branches here either: with a store under a branch the compiler moves the load down to it and waits for
     // it there)
-    auto place = [&](uint32_t k) -> uint4 * {
-        const uint32_t idx = piece_index(k);
-        return idx < nmeta ? meta4 + idx : lds4 + (idx - nmeta);
-    };
-    *place(0) = s0;
-    if constexpr (K > 1) *place(1) = s1;
-    if constexpr (K > 2) *place(2) = s2, *place(3) = s3;
+    auto put = [&](uint32_t idx, const uint4 &t) { *(idx < nmeta ? meta4 + idx : lds4 + (idx - nmeta)) = t; };
+    put(piece_index(0), s0);
+    if constexpr (K > 1) put(piece_index(1), s1);
+    if constexpr (K > 2) put(piece_index(2), s2), put(piece_index(3), s3);
     static_assert(K <= 4, "at most four pieces per thread are brought here");
-    for (uint32_t idx = tid + (uint32_t)K * nt; idx < ntot; idx += nt) {
-        if (idx < nmeta)
-            meta4[idx] = p4[idx];
-        else
-            lds4[idx - nmeta] = xsrc[idx - nmeta];
+    if constexpr (NB > 1) {
+        // four loads on their way per thread and round (a round is a trip to the L2 or beyond)
+        constexpr uint32_t U = NB == 2 || NB * VW >= 32 ? 1 : 4;
+        for (uint32_t idx = tid + (uint32_t)K * nt; idx < ntot; idx += U * nt) {
+            uint4 t[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t i = min(idx + u * nt, ntot - 1u);
+                t[u] = *(i < nmeta ? p4 + i : xsrc + (i - nmeta));
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t i = min(idx + u * nt, ntot - 1u);
+                put(i, t[u]);
+            }
+        }
+    } else {
+        for (uint32_t idx = tid + (uint32_t)K * nt; idx < ntot; idx += nt) {
+            if (idx < nmeta)
+                meta4[idx] = p4[idx];
+            else
+                lds4[idx - nmeta] = xsrc[idx - nmeta];
+        }
     }
     // what 16-byte pieces do not cover: the last n % 8 entries of x, or all of x if it is not 16-byte aligned or its
     // rows are longer than the NB values this launch takes
-    if (NB > 1 && ld != NB) {
+    if (NB > 1 && NB < 8 && ld != NB) {
         // one load of NB values per row of X where the alignment allows it (ld counts values of VW bytes)
         typedef uint16_t rowvec __attribute__((ext_vector_type(NB * VW / 2)));
         if ((reinterpret_cast<uintptr_t>(x) & (uint32_t)(VW * NB - 1)) == 0 && ld % NB == 0) {
             const rowvec *src = reinterpret_cast<const rowvec *>(x);
             rowvec *dst = reinterpret_cast<rowvec *>(xs);
-            for (uint32_t i = tid; i < it.n; i += nt) dst[i] = src[i * (ld / NB)];
+            const uint32_t step = ld / NB;
+            constexpr uint32_t U = NB * VW <= 8 ? 8 : 4;               // rows on their way per thread and round
+            for (uint32_t i = tid; i < it.n; i += U * nt) {
+                rowvec t[U];
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u) t[u] = src[(size_t)min(i + u * nt, it.n - 1u) * step];
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u) dst[min(i + u * nt, it.n - 1u)] = t[u];
+            }
         } else if constexpr (VW == 2) {
-            for (uint32_t i = tid; i < n; i += nt) xs[i] = x[(i / NB) * ld + (i % NB)];
+            for (uint32_t i = tid; i < n; i += nt) xs[i] = x[(size_t)(i / NB) * ld + (i % NB)];
         } else {
             const uint32_t *src = reinterpret_cast<const uint32_t *>(x);
             uint32_t *dst = reinterpret_cast<uint32_t *>(xs);
-            for (uint32_t i = tid; i < it.n * NB; i += nt) dst[i] = src[(i / NB) * ld + (i % NB)];
+            for (uint32_t i = tid; i < it.n * NB; i += nt) dst[i] = src[(size_t)(i / NB) * ld + (i % NB)];
         }
     } else {
         for (uint32_t i = (x_fast ? nvec * 8u : 0u) + tid; i < n; i += nt) xs[i] = x[i];
@@ -778,10 +889,12 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     if constexpr ((TM & 4) != 0) b8.run(c);
     if constexpr ((TM & 2) != 0) b4.run(c);
     if constexpr ((TM & 1) != 0) b2.run(c);
-    rs.run(c);
-    ECS_STAMP(c, 11);           // all chunks of this wavefront done
-    __syncthreads();
-    ECS_STAMP(c, 12);           // second barrier passed
+    if constexpr (NB == 1) {
+        rs.run(c);
+        ECS_STAMP(c, 11);           // all chunks of this wavefront done
+        __syncthreads();
+        ECS_STAMP(c, 12);           // second barrier passed
+    }
 
     // every row: add its slots and the partial sums of its lane units in a fixed order (16 lanes stride over them,
     // then a fixed tree), store FP16.  (Measured and not kept: a whole wavefront per row for long rows, 64 lanes
@@ -792,30 +905,75 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     const uint32_t *rowidx = reinterpret_cast<const uint32_t *>(meta + hdr[PH_ROWIDX_OFF]);   // the output row of each row
     const uint16_t *rowslot = reinterpret_cast<const uint16_t *>(meta + hdr[PH_ROWSLOT_OFF]);
     const uint32_t *rowlu = reinterpret_cast<const uint32_t *>(meta + hdr[PH_ROWLU_OFF]);
-    const float *part = slots + hdr[PH_NSLOTS] * NB;
+    const float *part = slots + hdr[PH_NSLOTS] * Partial<NB>::G;
     const uint32_t j = tid & 15;
-    for (uint32_t r = tid >> 4; r < nrows; r += nt >> 4) {
-        float sum[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) sum[b] = 0.0f;
-        if constexpr (TM != 0) {
-            const uint32_t s0 = rowslot[r], s1 = rowslot[r + 1];
-            for (uint32_t q = s0 + j; q < s1; q += 16)
-#pragma unroll
-                for (int b = 0; b < NB; ++b) sum[b] += slots[q * NB + b];
-        }
-        const uint32_t l0 = rowlu[r], l1 = rowlu[r + 1];
-        for (uint32_t q = l0 + j; q < l1; q += 16)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) sum[b] += part[q * NB + b];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const float t = row16_allreduce(sum[b]);
-            if constexpr (VW == 2) {
-                if (j == 0) y[rowidx[r] * ld + b] = __half_as_ushort(__float2half_rn(t));
-            } else {
-                if (j == 0) reinterpret_cast<float *>(y)[rowidx[r] * ld + b] = t;
+    if constexpr (NB == 1) {
+        for (uint32_t r = tid >> 4; r < nrows; r += nt >> 4) {
+            float sum = 0.0f;
+            if constexpr (TM != 0) {
+                const uint32_t s0 = rowslot[r], s1 = rowslot[r + 1];
+                for (uint32_t q = s0 + j; q < s1; q += 16) sum += slots[q];
             }
+            const uint32_t l0 = rowlu[r], l1 = rowlu[r + 1];
+            for (uint32_t q = l0 + j; q < l1; q += 16) sum += part[q];
+            const float t = row16_allreduce(sum);
+            if constexpr (VW == 2) {
+                if (j == 0) y[rowidx[r]] = __half_as_ushort(__float2half_rn(t));
+            } else {
+                if (j == 0) reinterpret_cast<float *>(y)[rowidx[r]] = t;
+            }
+        }
+    } else {
+        // Several right-hand sides: NB partial sums per lane unit are too much for LDS beside X on the larger panels, so
+        // the residual stream is taken in phases of `per_phase` chunks per wavefront (0: all in one).  After each phase
+        // the rows that end in it are finished; the one row that runs on leaves its 16 lanes' sums in `carry`.  Every
+        // lane adds the same numbers in the same order as with one phase: same bits.
+        const uint32_t all = (rs.nlanes + 63u) >> 6;
+        const uint32_t per = per_phase ? per_phase * c.nwaves : max(all, 1u);               // chunks per phase
+        for (uint32_t ph = 0, first = 0;; ++ph, first += per) {
+            rs.part0 = first;
+            rs.run_phase(c, ph * per_phase, per_phase ? (ph + 1u) * per_phase : rs.n);
+            __syncthreads();
+            const bool last = first + per >= all;
+            const uint32_t b = 64u * first, e = 64u * (first + per);
+            for (uint32_t r = tid >> 4; r < nrows; r += nt >> 4) {
+                const uint32_t l0 = rowlu[r], l1 = rowlu[r + 1];
+                const bool done = last || l1 <= e;
+                if ((ph && l1 <= b) || (!done && l0 >= e)) continue;            // finished before, or not begun
+                float sum[NB];
+#pragma unroll
+                for (int k = 0; k < NB; ++k) sum[k] = 0.0f;
+                uint32_t q = l0 + j;
+                if (ph && l0 < b) {
+#pragma unroll
+                    for (int k = 0; k < NB; ++k) sum[k] = carry[(((ph - 1u) & 1u) * 16u + j) * NB + k];
+                    q += (b - l0 - j + 15u + 16u) / 16u * 16u - 16u;              // its first lane unit in this phase
+                } else if constexpr (TM != 0) {
+                    const uint32_t s0 = rowslot[r], s1 = rowslot[r + 1];
+                    for (uint32_t s = s0 + j; s < s1; s += 16) Partial<NB>::add(slots, c.pstride, s, sum);
+                }
+                for (const uint32_t stop = min(l1, e); q < stop; q += 16) Partial<NB>::add(part, c.pstride, q - b, sum);
+                if (!done) {
+#pragma unroll
+                    for (int k = 0; k < NB; ++k) carry[((ph & 1u) * 16u + j) * NB + k] = sum[k];
+                    continue;
+                }
+                // every lane has every total: lane k stores the k-th
+                float out = 0.0f;
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    const float t = row16_allreduce(sum[k]);
+                    out = j == (uint32_t)k ? t : out;
+                }
+                if (j < (uint32_t)NB) {
+                    if constexpr (VW == 2)
+                        y[(size_t)rowidx[r] * ld + j] = __half_as_ushort(__float2half_rn(out));
+                    else
+                        reinterpret_cast<float *>(y)[(size_t)rowidx[r] * ld + j] = out;
+                }
+            }
+            if (last) break;
+            __syncthreads();                       // the partial sums of this phase have been read
         }
     }
 #ifdef ECS_TRACE
@@ -931,14 +1089,16 @@ static int launch_m(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
         if (e != hipSuccess) return (int)e;
         attr_set_for = lds_bytes;
     }
-    const uint32_t grid = batch.item[batch.count - 1].block_end;
+    // several right-hand sides: one workgroup per panel and group of NB columns, and the phases in place of the count
+    const uint32_t grid = NB > 1 ? batch.item[0].block_end * (batch.item[0].row_stride / NB) : batch.item[batch.count - 1].block_end;
+    const uint32_t first = NB > 1 ? batch.per_phase : batch.count;
 #ifdef ECS_TRACE
     const uint64_t trace_words = next_trace_region(grid);
 #else
     const uint64_t trace_words = 0;
 #endif
     hipLaunchKernelGGL((ecspmv_kernel<TM, DB, MODE, K, NB, VW>), dim3(grid), dim3(threads), lds_bytes, (hipStream_t)stream,
-                       batch.count, threads, batch.item[0].image, batch.item[0].x, batch.item[0].y, batch.item[0].n,
+                       first, threads, batch.item[0].image, batch.item[0].x, batch.item[0].y, batch.item[0].n,
                        batch.item[0].panel_stride, batch.item[0].meta_stride, batch.item[0].x_bytes, batch.item[0].block_end,
                        batch.item[0].row_stride, trace_words, batch);
     return (int)hipGetLastError();

@@ -14,11 +14,13 @@ struct EcsBatchItem {
     uint16_t *y;              // device, m FP16
     uint32_t n, panel_stride, meta_stride, x_bytes;
     uint32_t block_end;       // workgroups [previous item's block_end, block_end) belong to this item
-    uint32_t row_stride;      // several right-hand sides: elements from one row of X (and Y) to the next; 0 = packed
+    uint32_t row_stride;      // several right-hand sides: elements from one row of X (and Y) to the next
 };
 #define ECS_MAX_BATCH 16
 struct EcsBatch {
-    uint32_t count, pad_[3];
+    uint32_t count;
+    uint32_t per_phase;       // several right-hand sides: residual chunks per wavefront and phase; 0 = one phase
+    uint32_t pad_[2];
     EcsBatchItem item[ECS_MAX_BATCH];
 };
 static_assert(sizeof(EcsBatchItem) == 48 && sizeof(EcsBatch) == 16 + 48 * ECS_MAX_BATCH, "layout the kernel reads");
@@ -26,8 +28,9 @@ static_assert(sizeof(EcsBatchItem) == 48 && sizeof(EcsBatch) == 16 + 48 * ECS_MA
 // Launches one kernel for all items (count <= ECS_MAX_BATCH, same workgroup size for all).
 int launch_ecspmv(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, uint32_t type_mask, uint32_t delta_bits,
                   uint32_t value_bits, void *stream);
-// One matrix, nb = 2, 4 or 8 right-hand sides (x: n rows of nb values, y: m rows of nb values); type_mask must not
-// have the bit of the 16-grained set, nor that of the 8-grained set with FP32 values.
+// One matrix, nb = 2, 4 or 8 columns of X and Y per workgroup, row_stride / nb workgroups per panel (row_stride: values
+// from one row of X, and of Y, to the next); type_mask must not have the bit of the 16-grained set, nor that of the
+// 8-grained set with FP32 values.
 int launch_ecspmv_multi(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, uint32_t type_mask,
                         uint32_t delta_bits, uint32_t value_bits, uint32_t nb, void *stream);
 int launch_csr(const void *d_rowptr, const void *d_col, const void *d_val, const void *d_x, void *d_y, uint32_t m,
