@@ -55,6 +55,32 @@ int lds_limit(int *bytes)
     return 0;
 }
 
+// Workgroup size of a launch of `grid` workgroups in all that have `chunks` chunks between them (a wavefront takes one at
+// a time); `pieces`: 16-byte pieces of tables and x the widest of them brings to LDS; `sets`: the coarsest block set is
+// the `sets`-th.  Measured, cold, 256 panels unless said otherwise, us with 512 / 768 / 1024 threads:
+//   alone, up to 24 chunks: eight wavefronts are up and past the first barrier sooner, and two or three rounds are enough:
+//     2048 x 2048 at 30 % (10 chunks, 128 panels) 3.28 / 3.19 / 3.58, 3072 x 3072 at 40 %, 8-bit (22) 4.20 / 4.53 / 4.55,
+//     768 x 768 (8, 48 panels) 2.76 / 3.19 / 3.07;
+//   up to 48: twelve wavefronts, 5120 x 5120 at 30 % (30) 5.77 / 5.43 / 5.67, 4096 x 4096 at 50 %, 4-bit (43)
+//     6.38 / 5.90 / 6.18, 8-bit (44) 6.53 / 6.54 / 6.85; with two block sets (2- and 4-grained) a wavefront requests up to
+//     four chunks before it computes, and sixteen have all of them on the way at once: 5120 x 5120, 8-bit (45) 6.58 / 6.33 / 5.82;
+//   beyond, sixteen: 11008 x 4096 at 40 %, 4-bit (72) 10.27 / 10.06 / 9.48.
+//   Several matrices, 256 / 512 threads: small panels want more workgroups on a compute unit (its 2048 threads are eight
+//     workgroups of 256), 16 x 1024 x 1024 (7 chunks, 1024 workgroups) 5.08 / 5.97, 3 x 3072 x 3072 (15, 768) 7.00 / 7.19;
+//     larger ones, or few of them, want more wavefronts: 16 x 512 x 5120 (24, 512) 8.05 / 7.23, 3 x 768 x 768 (8, 144) 3.79 / 3.52.
+// Never so few threads that x takes more than the four pieces per thread that travel together: 512 x 20480 (17 chunks,
+//   2630 pieces) 5.12 / 4.66 / 5.15.
+uint32_t choose_threads(uint32_t grid, uint64_t chunks, uint32_t pieces, bool alone, uint32_t sets)
+{
+    uint32_t t;
+    if (alone)
+        t = chunks <= 24u * (uint64_t)grid ? 512u : chunks <= 48u * (uint64_t)grid && sets != 2u ? 768u : 1024u;
+    else
+        t = chunks <= 16u * (uint64_t)grid && grid >= 512u ? 256u : 512u;
+    while (pieces > 4u * t && t < (alone ? 1024u : 512u)) t += 256u;
+    return t;
+}
+
 int map_build_error(int e)
 {
     if (e == 0) return ECSPMV_OK;
@@ -326,7 +352,8 @@ int ecspmv_run_batch(const ecspmv_matrix *const *As, const void *const *d_xs, vo
         ecs::EcsBatch b;
         std::memset(&b, 0, sizeof(b));
         b.count = (uint32_t)nb;
-        uint32_t blocks = 0, lds = 0, mask = 0;
+        uint32_t blocks = 0, lds = 0, mask = 0, pieces = 0;
+        uint64_t chunks = 0;
         for (int32_t i = 0; i < nb; ++i) {
             const int32_t src = base + i;
             const ecs::Image &im = As[src]->image;
@@ -342,10 +369,10 @@ int ecspmv_run_batch(const ecspmv_matrix *const *As, const void *const *d_xs, vo
             it.block_end = blocks;
             lds = im.lds_bytes > lds ? im.lds_bytes : lds;
             mask |= im.type_mask;
+            chunks += im.total_chunks;
+            pieces = std::max(pieces, (im.meta_stride + it.x_bytes) / 16u);
         }
-        // Workgroup size: a lone SpMV gets one 1024-thread workgroup per compute unit; in a batch, 512-thread
-        // workgroups of neighbouring matrices share compute units and hide each other's start and end phases.
-        uint32_t threads = nb > 1 ? 512u : 1024u;
+        uint32_t threads = choose_threads(blocks, chunks, pieces, nb == 1, mask >= 8u ? 4u : mask >= 4u ? 3u : mask >= 2u ? 2u : mask);
         for (int32_t i = 0; i < nb; ++i) {
             const int t = As[base + i]->image.threads_per_wg;
             if (t) threads = (uint32_t)t;                      // a build-time choice overrides

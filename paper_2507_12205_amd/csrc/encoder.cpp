@@ -812,6 +812,7 @@ int build_image(const Csr &A, const BuildParams &bp, Image &out)
     }
     uint32_t stride = 256, meta = 16, slots = 1;
     out.max_block_slots = out.max_chunks = 0;
+    out.total_chunks = 0;
     for (auto &im : imgs) {
         if (im.err) return im.err;
         if (im.bytes.size() > 0xFFFFF000ull) return -2;                      // offsets inside a panel are 32-bit
@@ -819,7 +820,10 @@ int build_image(const Csr &A, const BuildParams &bp, Image &out)
         meta = std::max(meta, im.meta_bytes);
         slots = std::max(slots, im.lds_slots);
         out.max_block_slots = std::max(out.max_block_slots, im.nslots);
-        out.max_chunks = std::max(out.max_chunks, (im.lds_slots - im.nslots) / ECS_CHUNK_LANES);
+        const uint32_t rchunks = (im.lds_slots - im.nslots) / ECS_CHUNK_LANES;
+        out.max_chunks = std::max(out.max_chunks, rchunks);
+        out.total_chunks += rchunks;
+        for (int t = 1; t <= ECS_NUM_BTYPES; ++t) out.total_chunks += (uint64_t)(im.units_by_g[t] + 3) / 4;
     }
     meta = align_up(meta, 16);
     // 4 KB of zeros after the last panel: loads that stand in for missing chunks may run past a short last panel
