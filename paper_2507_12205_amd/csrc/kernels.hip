@@ -121,18 +121,17 @@ struct XWords {
     uint32_t w[NB * VW <= 4 ? 1 : NB * VW / 4];
     __device__ __forceinline__ void read(const uint16_t *xs, uint32_t col)
     {
-        const uint8_t *p = reinterpret_cast<const uint8_t *>(xs) + col * (NB * VW);
         if constexpr (NB * VW == 2) {
-            w[0] = *reinterpret_cast<const uint16_t *>(p);
+            w[0] = xs[col];
         } else if constexpr (NB * VW == 4) {
-            w[0] = *reinterpret_cast<const uint32_t *>(p);
+            w[0] = reinterpret_cast<const uint32_t *>(xs)[col];
         } else if constexpr (NB * VW == 8) {
-            const uint2 t = *reinterpret_cast<const uint2 *>(p);
+            const uint2 t = reinterpret_cast<const uint2 *>(xs)[col];
             w[0] = t.x, w[1] = t.y;
         } else {
 #pragma unroll
             for (int q = 0; q < NB * VW / 16; ++q) {
-                const uint4 t = reinterpret_cast<const uint4 *>(p)[q];
+                const uint4 t = reinterpret_cast<const uint4 *>(xs)[(NB * VW / 16) * col + q];
                 w[4 * q] = t.x, w[4 * q + 1] = t.y, w[4 * q + 2] = t.z, w[4 * q + 3] = t.w;
             }
         }
@@ -609,6 +608,14 @@ struct ResidualSet {
     __device__ __forceinline__ void run(const Ctx &c)
     {
         uint32_t i = 0;
+        if constexpr (DEPTH == 1) {
+            for (; i + 1u < n; ++i) {
+                step(c, i, 0);
+                load_chunk<DB, VW>(c, res_off, zero_off, chunk_of(c, i + 1u), nlanes, buf[0]);
+            }
+            if (i < n) step(c, i, 0);
+            return;
+        }
         for (; i + 2 * DEPTH - 1 < n; i += DEPTH) {
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) {
