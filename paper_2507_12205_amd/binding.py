@@ -147,6 +147,7 @@ class Matrix:
     def __init__(self, handle: int):
         self._h = c_void_p(handle)
         self.d_image = None          # whatever object owns the device buffer (kept alive here)
+        self.value_bits = self.ecspmv_stats().value_bits     # 16 or 32: a handle's values never change
 
     def __del__(self):
         try:

@@ -7,8 +7,11 @@ from . import binding as B
 
 
 def _stream_handle(stream=None) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    """The HIP stream to launch on: the given one, or the current one of the current device (asked for as a plain handle:
+    building torch's stream object takes 2.8 us, as long as the launch itself)."""
+    if stream is not None:
+        return int(stream.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def upload(mat: B.Matrix, device="cuda:0", stream=None) -> torch.Tensor:
@@ -23,7 +26,7 @@ def upload(mat: B.Matrix, device="cuda:0", stream=None) -> torch.Tensor:
 def run(mat: B.Matrix, x: torch.Tensor, y: torch.Tensor, stream=None) -> torch.Tensor:
     """y = W x on the given (or current) stream; x, y are CUDA tensors of length n, m: FP16, or FP32 for a matrix
     built from FP32 values."""
-    want = torch.float32 if mat.ecspmv_stats().value_bits == 32 else torch.float16
+    want = torch.float32 if mat.value_bits == 32 else torch.float16
     assert x.dtype == want and y.dtype == want and x.is_cuda and y.is_cuda
     assert x.is_contiguous() and y.is_contiguous()
     mat.ecspmv_run(x.data_ptr(), y.data_ptr(), _stream_handle(stream))
@@ -33,7 +36,7 @@ def run(mat: B.Matrix, x: torch.Tensor, y: torch.Tensor, stream=None) -> torch.T
 def run_multi(mat: B.Matrix, X: torch.Tensor, Y: torch.Tensor, stream=None) -> torch.Tensor:
     """Y = W X for X of shape (n, nb), Y of shape (m, nb), row-major, nb in {1, 2, 4, 8}; FP16, or FP32 for a matrix
     built from FP32 values."""
-    want = torch.float32 if mat.ecspmv_stats().value_bits == 32 else torch.float16
+    want = torch.float32 if mat.value_bits == 32 else torch.float16
     assert X.dtype == want and Y.dtype == want and X.is_cuda and Y.is_cuda
     assert X.dim() == 2 and Y.dim() == 2 and X.shape[1] == Y.shape[1] and X.is_contiguous() and Y.is_contiguous()
     mat.ecspmv_run_multi(X.data_ptr(), Y.data_ptr(), int(X.shape[1]), _stream_handle(stream))
