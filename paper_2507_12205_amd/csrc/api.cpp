@@ -1,6 +1,7 @@
 // C ABI of the library (see include/ecspmv.h): argument checks, option defaults, handle bookkeeping.
 #include <algorithm>
 #include <atomic>
+#include <cstddef>
 #include <cstring>
 #include <new>
 #include <vector>
@@ -350,7 +351,7 @@ int ecspmv_run_batch(const ecspmv_matrix *const *As, const void *const *d_xs, vo
             if (nx.delta_bits != bits || nx.value_bits != vbits) break;
         }
         ecs::EcsBatch b;
-        std::memset(&b, 0, sizeof(b));
+        std::memset(&b, 0, offsetof(ecs::EcsBatch, item) + sizeof(ecs::EcsBatchItem) * (size_t)(nb == 1 ? 1 : ECS_MAX_BATCH));
         b.count = (uint32_t)nb;
         uint32_t blocks = 0, lds = 0, mask = 0, pieces = 0;
         uint64_t chunks = 0;
@@ -426,7 +427,7 @@ int ecspmv_run_multi(const ecspmv_matrix *A, const void *d_X, void *d_Y, int32_t
         break;
     }
     ecs::EcsBatch b;
-    std::memset(&b, 0, sizeof(b));
+    std::memset(&b, 0, offsetof(ecs::EcsBatch, item) + sizeof(ecs::EcsBatchItem));       // the only item
     b.count = 1;
     b.per_phase = k;
     ecs::EcsBatchItem &it = b.item[0];
