@@ -67,7 +67,7 @@ typedef struct ecspmv_build_opts {
                                  where few long rows would put more partial sums into a panel than LDS holds) */
     int32_t  num_threads;     /* host threads for the offline phase; 0 = hardware concurrency, at most 16 */
     int32_t  threads_per_wg;  /* workgroup size of the SpMV launch, multiple of 64 in [64,1024]; 0 = chosen at
-                                 launch: 1024 for a lone SpMV, 512 inside a batch */
+                                 launch by the work in a panel: 512 to 1024 for a lone SpMV, 256 or 512 in a batch */
     uint64_t flags;           /* ECSPMV_FLAG_* */
 } ecspmv_build_opts;
 

@@ -68,7 +68,9 @@ int lds_limit(int *bytes)
 //   beyond, sixteen: 11008 x 4096 at 40 %, 4-bit (72) 10.27 / 10.06 / 9.48.
 //   Several matrices, 256 / 512 threads: small panels want more workgroups on a compute unit (its 2048 threads are eight
 //     workgroups of 256), 16 x 1024 x 1024 (7 chunks, 1024 workgroups) 5.08 / 5.97, 3 x 3072 x 3072 (15, 768) 7.00 / 7.19;
-//     larger ones, or few of them, want more wavefronts: 16 x 512 x 5120 (24, 512) 8.05 / 7.23, 3 x 768 x 768 (8, 144) 3.79 / 3.52.
+//     larger ones, or few of them, want more wavefronts: 16 x 512 x 5120 (24, 512) 8.05 / 7.23, 3 x 768 x 768 (8, 144) 3.79 / 3.52;
+//     with an 8-grained set a kernel takes 80 registers, and a compute unit holds three workgroups of 512 but seven of 256:
+//     16 x 1024 x 4096 at 50 %, 8-bit, 128 panels (22, 2048) 17.94 / 21.55, 8 x 4096 x 4096 (44, 2048) 30.73 / 31.95.
 // Never so few threads that x takes more than the four pieces per thread that travel together: 512 x 20480 (17 chunks,
 //   2630 pieces) 5.12 / 4.66 / 5.15.
 uint32_t choose_threads(uint32_t grid, uint64_t chunks, uint32_t pieces, bool alone, uint32_t sets)
@@ -77,7 +79,7 @@ uint32_t choose_threads(uint32_t grid, uint64_t chunks, uint32_t pieces, bool al
     if (alone)
         t = chunks <= 24u * (uint64_t)grid ? 512u : chunks <= 48u * (uint64_t)grid && sets != 2u ? 768u : 1024u;
     else
-        t = chunks <= 16u * (uint64_t)grid && grid >= 512u ? 256u : 512u;
+        t = (chunks <= 16u * (uint64_t)grid && grid >= 448u) || (sets >= 3u && grid >= 1024u) ? 256u : 512u;
     while (pieces > 4u * t && t < (alone ? 1024u : 512u)) t += 256u;
     return t;
 }
