@@ -408,7 +408,11 @@ int ecspmv_run_multi(const ecspmv_matrix *A, const void *d_X, void *d_Y, int32_t
     int lim = 0;
     int e = lds_limit(&lim);
     if (e) return hip_status(e);
-    const uint32_t threads = im.threads_per_wg ? (uint32_t)im.threads_per_wg : 1024u, waves = threads / 64u;
+    // Small panels: eight wavefronts, as with one vector (768 x 768, eight right-hand sides, 8 chunks per panel: 4.50 us with
+    // 1024 threads, 4.04 with 512; 2048 x 2048 at 30 %, 10 chunks: 5.30 and 4.95); larger ones sixteen (5120 x 5120, two,
+    // 30 chunks: 6.55 and 6.96).
+    const bool small = im.total_chunks <= 12u * (uint64_t)im.num_panels;
+    const uint32_t threads = im.threads_per_wg ? (uint32_t)im.threads_per_wg : small ? 512u : 1024u, waves = threads / 64u;
     // `per` columns of X and their partial sums sit in the LDS of a workgroup, so a panel takes nb / per workgroups, all
     // of one launch.  Where the partial sums of a whole panel do not fit beside X, the residual chunks are taken in
     // phases of k chunks per wavefront, and the partial sums of a phase are added up before the next one.

@@ -1,0 +1,91 @@
+"""The workgroup size a launch chooses from the work in its panels, and the staging of an x too wide for the first four
+pieces per thread: y does not depend on either, so every launch has the bits of one whose size the caller fixed."""
+import numpy as np
+import pytest
+
+from workloads import generators as gen
+from test_gpu_multi import E  # noqa: F401  -- the fixture
+
+pytestmark = pytest.mark.gpu
+
+
+def bits(t):
+    import torch
+    return t.view(torch.int16 if t.dtype == torch.float16 else torch.int32)
+
+
+def upload(E, W, **opts):  # noqa: F811
+    A = (E.ecspmv_build_dense_f32 if W.dtype == np.float32 else E.ecspmv_build_dense)(W, E.make_opts(**opts))
+    E.device.upload(A)
+    return A
+
+
+# chunks per panel (64 lane units of 16 entries, or 4 units of 64 columns) on both sides of 24 and of 48, with and without
+# block sets; more than 4096 pieces of x for the widest
+@pytest.mark.parametrize("m,n,density,panels,opts", [
+    (32, 640, 0.5, 2, dict(max_granularity=1)),                     # 5 chunks: 512 threads
+    (48, 4000, 0.25, 2, dict(max_granularity=1, delta_bits=4)),     # 24: the last that takes 512
+    (52, 4000, 0.25, 2, dict(max_granularity=1, delta_bits=4)),     # 26: 768
+    (48, 4000, 0.48, 2, dict(max_granularity=1)),                   # 45: 768
+    (48, 4001, 0.5, 2, dict(max_granularity=4)),                    # two block sets: 1024
+    (64, 4000, 0.5, 2, dict(max_granularity=1, delta_bits=4)),      # 63: 1024
+    (8, 40001, 0.02, 2, dict(max_granularity=1, delta_bits=4)),     # few chunks, 5000 pieces of x
+])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_alone_and_several_vectors(E, m, n, density, panels, opts, fp32):  # noqa: F811
+    import torch
+    if fp32 and n > 20000:
+        n = 20001
+    print(f"[case] {m}x{n} {opts} fp32={fp32}", flush=True)
+    W, x = gen.small_random(m, n, density, 7)
+    if opts["max_granularity"] > 1:
+        W[:, ::3] = np.float16(0.01)                                # columns that all rows share: block units
+    W = W.astype(np.float32) if fp32 else W
+    dt = torch.float32 if fp32 else torch.float16
+    A, B = upload(E, W, num_panels=panels, **opts), upload(E, W, num_panels=panels, threads_per_wg=1024, **opts)
+    xd = torch.from_numpy(x.astype(np.float32)).cuda().to(dt)
+    y, z = torch.full((m,), float("nan"), dtype=dt, device="cuda"), torch.empty(m, dtype=dt, device="cuda")
+    E.device.run(A, xd, y)
+    E.device.run(B, xd, z)
+    assert torch.equal(bits(y), bits(z))
+    ref = W.astype(np.float64) @ xd.cpu().numpy().astype(np.float64)
+    S = np.abs(W).astype(np.float64) @ np.abs(xd.cpu().numpy()).astype(np.float64)
+    assert (np.abs(y.cpu().numpy() - ref) <= 2e-3 * S + 1e-6).all()
+    if n < 5000:
+        X = torch.randn((n, 2), device="cuda").to(dt)
+        Y, Z = torch.full((m, 2), float("nan"), dtype=dt, device="cuda"), torch.empty((m, 2), dtype=dt, device="cuda")
+        E.device.run_multi(A, X, Y)
+        E.device.run_multi(B, X, Z)
+        assert torch.equal(bits(Y), bits(Z))
+
+
+# panels of all matrices, chunks per panel: 256 threads from 448 panels of at most 16 chunks on, or from 1024 panels with an
+# 8-grained set; otherwise 512; with 512, x of 20001 or 9001 entries takes up to six pieces per thread
+@pytest.mark.parametrize("count,m,n,density,panels,opts,fp32", [
+    (7, 128, 700, 0.3, 63, dict(max_granularity=1, delta_bits=4), False),
+    (7, 128, 700, 0.3, 64, dict(max_granularity=1, delta_bits=4), False),
+    (8, 128, 701, 0.3, 128, dict(max_granularity=8, flags=4), False),
+    (3, 30, 20001, 0.1, 5, dict(max_granularity=1, delta_bits=4), False),
+    (3, 30, 9001, 0.1, 5, dict(max_granularity=2), True),
+])
+def test_several_matrices(E, count, m, n, density, panels, opts, fp32):  # noqa: F811
+    import torch
+    print(f"[case] {count} x {m}x{n} panels={panels} {opts} fp32={fp32}", flush=True)
+    dt = torch.float32 if fp32 else torch.float16
+    mats, fixed, xs, ys = [], [], [], []
+    for k in range(count):
+        W, x = gen.small_random(m, n - k, density, 20 + k)
+        W = W.astype(np.float32) if fp32 else W
+        mats.append(upload(E, W, num_panels=panels, **opts))
+        fixed.append(upload(E, W, num_panels=panels, threads_per_wg=512, **opts))
+        buf = torch.zeros(n + 1, dtype=dt, device="cuda")
+        buf[k % 2:k % 2 + n - k].copy_(torch.from_numpy(x.astype(np.float32)).cuda())
+        xs.append(buf[k % 2:k % 2 + n - k])                         # every second x is off a 16-byte boundary
+        ys.append(torch.full((m,), float("nan"), dtype=dt, device="cuda"))
+    stream = torch.cuda.current_stream().cuda_stream
+    E.ecspmv_run_batch(mats, [x.data_ptr() for x in xs], [y.data_ptr() for y in ys], stream)
+    z = torch.empty(m, dtype=dt, device="cuda")
+    for A, x, y in zip(fixed, xs, ys):
+        A.ecspmv_run(x.data_ptr(), z.data_ptr(), stream)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(y), bits(z))
