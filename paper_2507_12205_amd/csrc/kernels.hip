@@ -771,8 +771,11 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // block set, 2 % of a step (7 % of a 5120 x 5120 launch) with two, 6 % with three; with many workgroups per
     // compute unit (MODE 2) requesting everything first is the faster order.  Several right-hand sides the same (4 % of a
     // launch with two on 4096 x 11008 at 8 bits); there it also keeps the kernels for two right-hand sides at 62 instead
-    // of 69 VGPRs, so that two workgroups share a compute unit where their LDS allows it.
-    constexpr bool residual_late = TM != 0 && !BATCH && (VW == 2 || NB > 1);
+    // of 69 VGPRs, so that two workgroups share a compute unit where their LDS allows it.  FP32 values
+    // the same where x comes with two pieces per thread (8-bit: 4096 x 4096 at 40 % 8.26 -> 7.72 us, 5120 x 5120 at 30 %
+    // 9.47 -> 9.02); a wider x holds the barrier up by itself, and the residual set is better under way (4096 x 11008,
+    // four pieces: 15.49 -> 15.57).
+    constexpr bool residual_late = TM != 0 && !BATCH && (VW == 2 || NB > 1 || K < 4);
     const uint4 *p4 = reinterpret_cast<const uint4 *>(panel);
     const uint32_t nmeta = meta_stride / 16u;
     const uint32_t nvec = n / 8u;
@@ -1163,7 +1166,7 @@ static int launch_k(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
     return (int)hipErrorInvalidValue;          // several right-hand sides: one matrix per launch
 }
 
-template <int TM, int DB, bool BATCH>
+template <int TM, int DB, bool BATCH, int VW = 2>
 static int launch_b(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, void *stream)
 {
     // staging pieces per thread: the largest [tables | x] list of the batch over the workgroup size
@@ -1171,24 +1174,25 @@ static int launch_b(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
     for (uint32_t i = 0; i < batch.count; ++i) {
         const EcsBatchItem &it = batch.item[i];
         const bool aligned = (reinterpret_cast<uintptr_t>(it.x) & 15) == 0;
-        const uint32_t pieces = it.meta_stride / 16u + (aligned ? it.n / 8u : 0u);
+        const uint32_t pieces = it.meta_stride / 16u + (aligned ? it.n / (16u / VW) : 0u);
         most = pieces > most ? pieces : most;
     }
     const uint32_t per_thread = (most + threads - 1) / threads;
-    if (per_thread <= 1) return launch_k<TM, DB, BATCH, 1, 1>(batch, threads, lds_bytes, stream);
-    if (per_thread <= 2) return launch_k<TM, DB, BATCH, 2, 1>(batch, threads, lds_bytes, stream);
-    return launch_k<TM, DB, BATCH, 4, 1>(batch, threads, lds_bytes, stream);
+    if constexpr (VW == 2)
+        if (per_thread <= 1) return launch_k<TM, DB, BATCH, 1, 1>(batch, threads, lds_bytes, stream);
+    if (per_thread <= 2) return launch_k<TM, DB, BATCH, 2, 1, VW>(batch, threads, lds_bytes, stream);
+    return launch_k<TM, DB, BATCH, 4, 1, VW>(batch, threads, lds_bytes, stream);
 }
 
 template <int TM>
 static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, uint32_t delta_bits, uint32_t value_bits,
                      void *stream)
 {
-    // FP32 values: one variant per set mask and delta width (widest staging, lone-launch buffer depths)
+    // FP32 values: lone-launch buffer depths
     if (value_bits == 32) {
         if (delta_bits == 16) return (int)hipErrorInvalidValue;
-        return delta_bits == 4 ? launch_k<TM, 4, false, 4, 1, 4>(batch, threads, lds_bytes, stream)
-                               : launch_k<TM, 8, false, 4, 1, 4>(batch, threads, lds_bytes, stream);
+        return delta_bits == 4 ? launch_b<TM, 4, false, 4>(batch, threads, lds_bytes, stream)
+                               : launch_b<TM, 8, false, 4>(batch, threads, lds_bytes, stream);
     }
     // index compression switched off (absolute 16-bit columns): the ablation point, one variant per set mask
     if (delta_bits == 16) return launch_k<TM, 16, false, 4, 1>(batch, threads, lds_bytes, stream);
