@@ -62,9 +62,11 @@ int lds_limit(int *bytes)
 //   alone, up to 24 chunks: eight wavefronts are up and past the first barrier sooner, and two or three rounds are enough:
 //     2048 x 2048 at 30 % (10 chunks, 128 panels) 3.28 / 3.19 / 3.58, 3072 x 3072 at 40 %, 8-bit (22) 4.20 / 4.53 / 4.55,
 //     768 x 768 (8, 48 panels) 2.76 / 3.19 / 3.07;
-//   up to 48: twelve wavefronts, 5120 x 5120 at 30 % (30) 5.77 / 5.43 / 5.67, 4096 x 4096 at 50 %, 4-bit (43)
-//     6.38 / 5.90 / 6.18, 8-bit (44) 6.53 / 6.54 / 6.85; with two block sets (2- and 4-grained) a wavefront requests up to
-//     four chunks before it computes, and sixteen have all of them on the way at once: 5120 x 5120, 8-bit (45) 6.58 / 6.33 / 5.82;
+//   up to 48, images with block sets: twelve wavefronts, 4096 x 4096 at 50 %, 4-bit (43) 6.38 / 5.90 / 6.18, 8-bit (44)
+//     6.53 / 6.54 / 6.85 (launches from the host one after the other: 6.06 against 6.30 with sixteen); but with two sets (2-
+//     and 4-grained) a wavefront requests up to four chunks before it computes, and sixteen have all of them on the way
+//     at once: 5120 x 5120, 8-bit (45) 6.58 / 6.33 / 5.82; and without sets, launched from the host, seven products of a 13B
+//     layer, four of them 5120 x 5120 (30), take 52.03 us with twelve for those four and 51.83 with sixteen;
 //   beyond, sixteen: 11008 x 4096 at 40 %, 4-bit (72) 10.27 / 10.06 / 9.48.
 //   Several matrices, 256 / 512 threads: small panels want more workgroups on a compute unit (its 2048 threads are eight
 //     workgroups of 256), 16 x 1024 x 1024 (7 chunks, 1024 workgroups) 5.08 / 5.97, 3 x 3072 x 3072 (15, 768) 7.00 / 7.19;
@@ -77,7 +79,7 @@ uint32_t choose_threads(uint32_t grid, uint64_t chunks, uint32_t pieces, bool al
 {
     uint32_t t;
     if (alone)
-        t = chunks <= 24u * (uint64_t)grid ? 512u : chunks <= 48u * (uint64_t)grid && sets != 2u ? 768u : 1024u;
+        t = chunks <= 24u * (uint64_t)grid ? 512u : chunks <= 48u * (uint64_t)grid && (sets == 1u || sets >= 3u) ? 768u : 1024u;
     else
         t = (chunks <= 16u * (uint64_t)grid && grid >= 448u) || (sets >= 3u && grid >= 1024u) ? 256u : 512u;
     while (pieces > 4u * t && t < (alone ? 1024u : 512u)) t += 256u;

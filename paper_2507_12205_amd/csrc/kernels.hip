@@ -845,9 +845,10 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // With K < 4 the list is covered (the launch counts its pieces); what is left with K = 4 comes in rounds of U loads per
     // thread that travel together (a round is a trip to the L2 or beyond).  One vector: two, as far as the registers of the
     // launches with several matrices go: three 5120 x 20480 in one launch 32.2 -> 30.2 us, two 19.9 -> 19.6; four: 29.8, but
-    // FP32 sixteen 1000 x 10000 16.5 -> 18.7.
+    // FP32 sixteen 1000 x 10000 16.5 -> 18.7.  A launch of one matrix has more threads and hardly ever gets here: one at
+    // a time, the code around it is then 1 % faster (5120 x 20480 10.90 -> 10.79).
     if constexpr (K == 4) {
-        constexpr uint32_t U = NB == 1 ? 2 : NB == 2 || NB * VW >= 32 ? 1 : 4;
+        constexpr uint32_t U = NB == 1 ? (LONE ? 1 : 2) : NB == 2 || NB * VW >= 32 ? 1 : 4;
         for (uint32_t idx = tid + (uint32_t)K * nt; idx < ntot; idx += U * nt) {
             uint4 t[U];
 #pragma unroll

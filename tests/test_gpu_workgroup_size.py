@@ -25,9 +25,10 @@ def upload(E, W, **opts):  # noqa: F811
 @pytest.mark.parametrize("m,n,density,panels,opts", [
     (32, 640, 0.5, 2, dict(max_granularity=1)),                     # 5 chunks: 512 threads
     (48, 4000, 0.25, 2, dict(max_granularity=1, delta_bits=4)),     # 24: the last that takes 512
-    (52, 4000, 0.25, 2, dict(max_granularity=1, delta_bits=4)),     # 26: 768
-    (48, 4000, 0.48, 2, dict(max_granularity=1)),                   # 45: 768
-    (48, 4001, 0.5, 2, dict(max_granularity=4)),                    # two block sets: 1024
+    (52, 4000, 0.25, 2, dict(max_granularity=1, delta_bits=4)),     # 26: 1024, no block sets
+    (18, 4000, 0.4, 2, dict(max_granularity=2)),                    # one block set: 768
+    (48, 4000, 0.48, 2, dict(max_granularity=1)),                   # 45: 1024
+    (20, 4001, 0.4, 2, dict(max_granularity=4)),                    # two block sets: 1024
     (64, 4000, 0.5, 2, dict(max_granularity=1, delta_bits=4)),      # 63: 1024
     (8, 40001, 0.02, 2, dict(max_granularity=1, delta_bits=4)),     # few chunks, 5000 pieces of x
 ])
