@@ -1103,19 +1103,29 @@ struct KernelArgs {
 };
 static_assert(offsetof(KernelArgs<EcsBatch>, table) == 64, "where the kernel reads the table");
 
-// handle of a kernel on the current device, asked for once per device and kept as long as the library is loaded
+// handle of a kernel on the device of `stream` (the null stream: the current one), which need not be the current device;
+// asked for once per device and kept as long as the library is loaded
 template <auto KERNEL>
-static int kernel_handle(hipFunction_t *f)
+static int kernel_handle(void *stream, hipFunction_t *f)
 {
     constexpr int kMaxDev = 64;
     static std::atomic<hipFunction_t> cached[kMaxDev];
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    int current = 0, dev = 0;
+    hipError_t e = hipGetDevice(&current);
+    if (e != hipSuccess) return (int)e;
+    dev = current;
+    if (stream) e = hipStreamGetDevice((hipStream_t)stream, &dev);
     if (e != hipSuccess) return (int)e;
     const bool keep = dev >= 0 && dev < kMaxDev;
     if (keep) *f = cached[dev].load(std::memory_order_acquire);
     if (*f) return 0;
+    if (dev != current) e = hipSetDevice(dev);             // symbols are looked up on the current device
+    if (e != hipSuccess) return (int)e;
     e = hipGetFuncBySymbol(f, reinterpret_cast<const void *>(KERNEL));
+    if (dev != current) {
+        const hipError_t back = hipSetDevice(current);
+        if (e == hipSuccess) e = back;
+    }
     if (e != hipSuccess) return (int)e;
     if (keep) cached[dev].store(*f, std::memory_order_release);
     return 0;
@@ -1140,15 +1150,18 @@ static int launch_m(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
 #else
     const uint64_t trace_words = 0;
 #endif
-    // The arguments are handed over as they lie in memory, and the kernel by its handle on the current device, looked up
+    // The arguments are handed over as they lie in memory, and the kernel by its handle on the stream's device, looked up
     // once: a launch then takes the host 2.25 us, against 2.7 us as a list of arguments with the table.
     const EcsBatchItem &it = batch.item[0];
     KernelArgs<Table> args = {first, threads, it.image, it.x, it.y, it.n, it.panel_stride, it.meta_stride, it.x_bytes,
                               it.block_end, it.row_stride, trace_words, {}};
     if constexpr (MODE != 0) args.table = batch;
     hipFunction_t f = nullptr;
-    const int e = kernel_handle<ecspmv_kernel<TM, DB, MODE, K, NB, VW>>(&f);
-    if (e) return e;
+    const int e = kernel_handle<ecspmv_kernel<TM, DB, MODE, K, NB, VW>>(stream, &f);
+    if (e) {
+        (void)hipGetLastError();                           // as below
+        return e;
+    }
     size_t bytes = sizeof(args);
     void *extra[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &args, HIP_LAUNCH_PARAM_BUFFER_SIZE, &bytes, HIP_LAUNCH_PARAM_END};
     const hipError_t s = hipModuleLaunchKernel(f, grid, 1, 1, threads, 1, 1, lds_bytes, (hipStream_t)stream, nullptr, extra);
