@@ -538,9 +538,10 @@ __device__ __forceinline__ void compute_chunk(const Ctx &c, const EcsRChunk *rch
         if constexpr (VW == 2) return half_bits_to_float((i & 1) ? (vw[i >> 1] >> 16) : (vw[i >> 1] & 0xFFFFu));
         else return __uint_as_float(vw[i]);
     };
-    // several right-hand sides: eight entries' x values on their way at a time (sixteen need more registers and are no
-    // faster, four are 1 % slower with four right-hand sides)
-    constexpr int GB = NB == 1 ? 16 : 8;
+    // Four or eight right-hand sides: eight entries' x values on their way at a time (sixteen need more registers and are no
+    // faster, four are 1 % slower with four).  Two: all sixteen, and nothing keeps the next chunk's loads behind these
+    // sums: 7308 x 8992 at 31 %, 4-bit 11.23 -> 10.81 us, FP32 4096 x 8192 at 30 % 9.82 -> 9.57.
+    constexpr int GB = NB <= 2 ? 16 : 8;
 #pragma unroll
     for (int g = 0; g < 16; g += GB) {
         XWords<NB, VW> xv[GB];
@@ -595,7 +596,7 @@ struct ResidualSet {
     {
         if (k < 3) ECS_TRACE_DRAIN(c, 5 + 2 * k);
         if (k < 3) ECS_STAMP(c, 5 + 2 * k);
-        compute_chunk<DB, FENCE, NB, VW>(c, rch, ren, part, chunk_of(c, k), chunk_of(c, k) - (NB > 1 ? part0 : 0u), buf[d]);
+        compute_chunk<DB, FENCE, NB, VW>(c, rch, ren, part, chunk_of(c, k), chunk_of(c, k) - (NB > 2 ? part0 : 0u), buf[d]);
         if (k < 3) ECS_STAMP(c, 6 + 2 * k);
     }
     // chunks i0 .. i1 - 1 of this wavefront (one buffer): a wavefront's next chunk, be it in the next phase, is on its
@@ -648,7 +649,9 @@ struct NoTable {};
 // compiled in: every instruction on the way to a wavefront's first loads counts, the scalar unit of a compute unit
 // issues one instruction per cycle for all 16 wavefronts), 1 = several SpMVs, 2 = several SpMVs with the buffer
 // depths that suit many workgroups per compute unit (residual-only images: deeper buffers; one block set: everything
-// requested before the first barrier);
+// requested before the first barrier), 3 = one SpMV with four or eight right-hand sides whose residual chunks are taken in
+// phases (a mode of its own: the loop over phases costs launches that need one phase only 2-9 %, two vectors on
+// 16384 x 1024, 4-bit 6.5 us without it and 7.1 with it, 768 x 768 with four 3.56 and 3.76);
 // K: 16-byte pieces of [tables | x] each thread brings to LDS before the generic loop takes the rest;
 // NB: right-hand sides handled at once (x holds n rows of NB values, y m rows of NB values);
 // VW: bytes per value of W, x and y (2 = FP16, 4 = FP32)
@@ -658,7 +661,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
                                                       const uint32_t panel_stride0, const uint32_t meta_stride0,
                                                       const uint32_t x_bytes0, const uint32_t block_end0,
                                                       const uint32_t row_stride0, const uint64_t trace_words,
-                                                      const std::conditional_t<MODE == 0, NoTable, ecs::EcsBatch> batch)
+                                                      const std::conditional_t<MODE == 0 || MODE == 3, NoTable, ecs::EcsBatch> batch)
 {
 #ifdef ECS_TRACE
     const uint64_t t_start = __builtin_amdgcn_s_memtime(), t_start_real = __builtin_amdgcn_s_memrealtime();
@@ -668,7 +671,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // plain values the hardware can hand over in registers; the table behind them is read only by launches that
     // carry several SpMVs: one 16-byte vector load per lane fetches all of it (scalar loads by every wavefront of a
     // workgroup are served one wavefront after the other), and the item is then read out of the lanes.
-    constexpr bool BATCH = MODE == 2, LONE = MODE == 0;
+    constexpr bool BATCH = MODE == 2, LONE = MODE == 0 || MODE == 3, PHASES = MODE == 3;
     ecs::EcsBatchItem it;
     it.image = image0, it.x = x0, it.y = y0, it.n = n0, it.panel_stride = panel_stride0, it.meta_stride = meta_stride0;
     it.x_bytes = x_bytes0, it.block_end = block_end0, it.row_stride = 0;
@@ -720,13 +723,11 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     uint16_t *xs = reinterpret_cast<uint16_t *>(lds);
     uint8_t *meta = lds + x_bytes;
     float *slots = reinterpret_cast<float *>(lds + x_bytes + meta_stride);
-    // several right-hand sides: chunks a wavefront takes per phase (the count of matrices is 1), and with more than one
-    // phase the 16 lanes' sums of the row that runs on into the next phase, kept for two phases in turn
+    // phases: chunks a wavefront takes per phase (the count of matrices is 1), and the 16 lanes' sums of the row that runs
+    // on into the next phase, kept for two phases in turn
     const uint32_t per_phase = count;
     float *carry = slots;
-    if constexpr (NB > 1) {
-        if (per_phase) slots += 2 * 16 * NB;
-    }
+    if constexpr (PHASES) slots += 2 * 16 * NB;
 
     const uint32_t tid = threadIdx.x, nt = threads;
     const uint8_t *panel = it.image + ECS_IMAGE_HEADER + (size_t)it.panel_stride * panel_index;
@@ -770,12 +771,13 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // chunks are computed while the residual chunk travels (run_first).  Measured: 3-5 % of a lone launch with one
     // block set, 2 % of a step (7 % of a 5120 x 5120 launch) with two, 6 % with three; with many workgroups per
     // compute unit (MODE 2) requesting everything first is the faster order.  Several right-hand sides the same (4 % of a
-    // launch with two on 4096 x 11008 at 8 bits); there it also keeps the kernels for two right-hand sides at 62 instead
-    // of 69 VGPRs, so that two workgroups share a compute unit where their LDS allows it.  FP32 values
+    // launch with two on 4096 x 11008 at 8 bits, FP32 4096 x 4096 at 8 bits 8.55 -> 7.97 us with two, at 4 bits 9.12 -> 8.49
+    // with four), but with two right-hand sides and one block set the residual set is better under way (16384 x 1024,
+    // 4-bit 6.75 -> 6.27 us, FP32 4096 x 4096, 4-bit 8.18 -> 7.51).  FP32 values
     // the same where x comes with two pieces per thread (8-bit: 4096 x 4096 at 40 % 8.26 -> 7.72 us, 5120 x 5120 at 30 %
     // 9.47 -> 9.02); a wider x holds the barrier up by itself, and the residual set is better under way (4096 x 11008,
     // four pieces: 15.49 -> 15.57).
-    constexpr bool residual_late = TM != 0 && !BATCH && (VW == 2 || NB > 1 || K < 4);
+    constexpr bool residual_late = TM != 0 && !BATCH && (NB > 1 ? NB > 2 || TM > 1 : VW == 2 || K < 4);
     const uint4 *p4 = reinterpret_cast<const uint4 *>(panel);
     const uint32_t nmeta = meta_stride / 16u;
     const uint32_t nvec = n / 8u;
@@ -814,7 +816,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     }
 
     if constexpr (NB > 1) {
-        const uint32_t chunks = per_phase ? per_phase * c.nwaves : (hdr[PH_NRLANES] + 63u) >> 6;      // of a phase
+        const uint32_t chunks = PHASES ? per_phase * c.nwaves : (hdr[PH_NRLANES] + 63u) >> 6;         // of a phase
         c.pstride = hdr[PH_NSLOTS] + 64u * chunks;
     }
 
@@ -900,7 +902,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     if constexpr ((TM & 4) != 0) b8.run(c);
     if constexpr ((TM & 2) != 0) b4.run(c);
     if constexpr ((TM & 1) != 0) b2.run(c);
-    if constexpr (NB == 1) {
+    if constexpr (!PHASES) {
         rs.run(c);
         ECS_STAMP(c, 11);           // all chunks of this wavefront done
         __syncthreads();
@@ -935,56 +937,69 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
             }
         }
     } else {
-        // Several right-hand sides: NB partial sums per lane unit are too much for LDS beside X on the larger panels, so
-        // the residual stream is taken in phases of `per_phase` chunks per wavefront (0: all in one).  After each phase
-        // the rows that end in it are finished; the one row that runs on leaves its 16 lanes' sums in `carry`.  Every
-        // lane adds the same numbers in the same order as with one phase: same bits.
-        const uint32_t all = (rs.nlanes + 63u) >> 6;
-        const uint32_t per = per_phase ? per_phase * c.nwaves : max(all, 1u);               // chunks per phase
-        for (uint32_t ph = 0, first = 0;; ++ph, first += per) {
-            rs.part0 = first;
-            rs.run_phase(c, ph * per_phase, per_phase ? (ph + 1u) * per_phase : rs.n);
-            __syncthreads();
-            const bool last = first + per >= all;
-            const uint32_t b = 64u * first, e = 64u * (first + per);
-            for (uint32_t r = tid >> 4; r < nrows; r += nt >> 4) {
-                const uint32_t l0 = rowlu[r], l1 = rowlu[r + 1];
-                const bool done = last || l1 <= e;
-                if ((ph && l1 <= b) || (!done && l0 >= e)) continue;            // finished before, or not begun
-                float sum[NB];
+        // every lane has every total: lane k stores the k-th
+        auto store = [&](uint32_t r, const float (&sum)[NB]) {
+            float out = 0.0f;
 #pragma unroll
-                for (int k = 0; k < NB; ++k) sum[k] = 0.0f;
-                uint32_t q = l0 + j;
-                if (ph && l0 < b) {
-#pragma unroll
-                    for (int k = 0; k < NB; ++k) sum[k] = carry[(((ph - 1u) & 1u) * 16u + j) * NB + k];
-                    q += (b - l0 - j + 15u + 16u) / 16u * 16u - 16u;              // its first lane unit in this phase
-                } else if constexpr (TM != 0) {
-                    const uint32_t s0 = rowslot[r], s1 = rowslot[r + 1];
-                    for (uint32_t s = s0 + j; s < s1; s += 16) Partial<NB>::add(slots, c.pstride, s, sum);
-                }
-                for (const uint32_t stop = min(l1, e); q < stop; q += 16) Partial<NB>::add(part, c.pstride, q - b, sum);
-                if (!done) {
-#pragma unroll
-                    for (int k = 0; k < NB; ++k) carry[((ph & 1u) * 16u + j) * NB + k] = sum[k];
-                    continue;
-                }
-                // every lane has every total: lane k stores the k-th
-                float out = 0.0f;
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const float t = row16_allreduce(sum[k]);
-                    out = j == (uint32_t)k ? t : out;
-                }
-                if (j < (uint32_t)NB) {
-                    if constexpr (VW == 2)
-                        y[(size_t)rowidx[r] * ld + j] = __half_as_ushort(__float2half_rn(out));
-                    else
-                        reinterpret_cast<float *>(y)[(size_t)rowidx[r] * ld + j] = out;
-                }
+            for (int k = 0; k < NB; ++k) {
+                const float t = row16_allreduce(sum[k]);
+                out = j == (uint32_t)k ? t : out;
             }
-            if (last) break;
-            __syncthreads();                       // the partial sums of this phase have been read
+            if (j < (uint32_t)NB) {
+                if constexpr (VW == 2)
+                    y[(size_t)rowidx[r] * ld + j] = __half_as_ushort(__float2half_rn(out));
+                else
+                    reinterpret_cast<float *>(y)[(size_t)rowidx[r] * ld + j] = out;
+            }
+        };
+        if constexpr (!PHASES) {
+            for (uint32_t r = tid >> 4; r < nrows; r += nt >> 4) {
+                float sum[NB] = {};
+                if constexpr (TM != 0) {
+                    const uint32_t s0 = rowslot[r], s1 = rowslot[r + 1];
+                    for (uint32_t q = s0 + j; q < s1; q += 16) Partial<NB>::add(slots, c.pstride, q, sum);
+                }
+                const uint32_t l0 = rowlu[r], l1 = rowlu[r + 1];
+                for (uint32_t q = l0 + j; q < l1; q += 16) Partial<NB>::add(part, c.pstride, q, sum);
+                store(r, sum);
+            }
+        } else {
+            // NB partial sums per lane unit are too much for LDS beside X on the larger panels, so the residual stream is
+            // taken in phases of `per_phase` chunks per wavefront.  After each phase the rows that end in it are finished;
+            // the one row that runs on leaves its 16 lanes' sums in `carry`.  Every lane adds the same numbers in the same
+            // order as with one phase: same bits.
+            const uint32_t all = (rs.nlanes + 63u) >> 6, per = per_phase * c.nwaves;        // chunks: of the panel, of a phase
+            for (uint32_t ph = 0, first = 0;; ++ph, first += per) {
+                rs.part0 = first;
+                rs.run_phase(c, ph * per_phase, (ph + 1u) * per_phase);
+                __syncthreads();
+                const bool last = first + per >= all;
+                const uint32_t b = 64u * first, e = 64u * (first + per);
+                for (uint32_t r = tid >> 4; r < nrows; r += nt >> 4) {
+                    const uint32_t l0 = rowlu[r], l1 = rowlu[r + 1];
+                    const bool done = last || l1 <= e;
+                    if ((ph && l1 <= b) || (!done && l0 >= e)) continue;        // finished before, or not begun
+                    float sum[NB] = {};
+                    uint32_t q = l0 + j;
+                    if (ph && l0 < b) {
+#pragma unroll
+                        for (int k = 0; k < NB; ++k) sum[k] = carry[(((ph - 1u) & 1u) * 16u + j) * NB + k];
+                        q += (b - l0 - j + 15u + 16u) / 16u * 16u - 16u;          // its first lane unit in this phase
+                    } else if constexpr (TM != 0) {
+                        const uint32_t s0 = rowslot[r], s1 = rowslot[r + 1];
+                        for (uint32_t s = s0 + j; s < s1; s += 16) Partial<NB>::add(slots, c.pstride, s, sum);
+                    }
+                    for (const uint32_t stop = min(l1, e); q < stop; q += 16) Partial<NB>::add(part, c.pstride, q - b, sum);
+                    if (!done) {
+#pragma unroll
+                        for (int k = 0; k < NB; ++k) carry[((ph & 1u) * 16u + j) * NB + k] = sum[k];
+                        continue;
+                    }
+                    store(r, sum);
+                }
+                if (last) break;
+                __syncthreads();                   // the partial sums of this phase have been read
+            }
         }
     }
 #ifdef ECS_TRACE
@@ -1134,7 +1149,7 @@ static int kernel_handle(void *stream, hipFunction_t *f)
 template <int TM, int DB, int MODE, int K, int NB, int VW = 2>
 static int launch_m(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, void *stream)
 {
-    typedef std::conditional_t<MODE == 0, NoTable, EcsBatch> Table;
+    typedef std::conditional_t<MODE == 0 || MODE == 3, NoTable, EcsBatch> Table;
     static thread_local uint32_t attr_set_for = 0;
     if (lds_bytes > 65536 && lds_bytes > attr_set_for) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(ecspmv_kernel<TM, DB, MODE, K, NB, VW>),
@@ -1155,7 +1170,7 @@ static int launch_m(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
     const EcsBatchItem &it = batch.item[0];
     KernelArgs<Table> args = {first, threads, it.image, it.x, it.y, it.n, it.panel_stride, it.meta_stride, it.x_bytes,
                               it.block_end, it.row_stride, trace_words, {}};
-    if constexpr (MODE != 0) args.table = batch;
+    if constexpr (MODE == 1 || MODE == 2) args.table = batch;
     hipFunction_t f = nullptr;
     const int e = kernel_handle<ecspmv_kernel<TM, DB, MODE, K, NB, VW>>(stream, &f);
     if (e) {
@@ -1175,6 +1190,8 @@ template <int TM, int DB, bool BATCH, int K, int NB, int VW = 2>
 static int launch_k(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, void *stream)
 {
     if constexpr (BATCH) return launch_m<TM, DB, 2, K, NB, VW>(batch, threads, lds_bytes, stream);
+    if constexpr (NB > 2)                     // (two right-hand sides are refused where they do not fit in one phase)
+        if (batch.per_phase) return launch_m<TM, DB, 3, K, NB, VW>(batch, threads, lds_bytes, stream);
     if (batch.count == 1) return launch_m<TM, DB, 0, K, NB, VW>(batch, threads, lds_bytes, stream);
     if constexpr (NB == 1) return launch_m<TM, DB, 1, K, NB, VW>(batch, threads, lds_bytes, stream);
     return (int)hipErrorInvalidValue;          // several right-hand sides: one matrix per launch
