@@ -498,8 +498,9 @@ __device__ __forceinline__ void compute_chunk(const Ctx &c, const EcsRChunk *rch
         for (int i = 0; i < 16; ++i) rel[i] = (r.d[i / 2] >> (16 * (i % 2))) & 0xFFFFu;
     } else {
         uint32_t run = 0;
-        if constexpr (DB == 4) {
-            // as above, not doubled: byte k of a word is the prefix up to nibble 2k + 1 (or 2k), at most 120
+        if constexpr (DB == 4 && NB > 1) {
+            // as above, not doubled: byte k of a word is the prefix up to nibble 2k + 1 (or 2k), at most 120 (FP32 values with
+            // one vector: the plain sum below is faster, 11008 x 4096 14.62 us against 14.77, 16384 x 2048 11.50 against 11.69)
             constexpr uint32_t M = 0x0F0F0F0Fu;
 #pragma unroll
             for (int w = 0; w < 2; ++w) {
@@ -517,7 +518,7 @@ __device__ __forceinline__ void compute_chunk(const Ctx &c, const EcsRChunk *rch
             // lane-local inclusive prefix of the 16 deltas
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                run += (r.d[i / 4] >> (8 * (i % 4))) & 0xFFu;
+                run += (r.d[i / (32 / DB)] >> (DB * (i % (32 / DB)))) & ((1u << DB) - 1u);
                 rel[i] = run;
             }
         }
@@ -773,11 +774,13 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // compute unit (MODE 2) requesting everything first is the faster order.  Several right-hand sides the same (4 % of a
     // launch with two on 4096 x 11008 at 8 bits, FP32 4096 x 4096 at 8 bits 8.55 -> 7.97 us with two, at 4 bits 9.12 -> 8.49
     // with four), but with two right-hand sides and one block set the residual set is better under way (16384 x 1024,
-    // 4-bit 6.75 -> 6.27 us, FP32 4096 x 4096, 4-bit 8.18 -> 7.51).  FP32 values
-    // the same where x comes with two pieces per thread (8-bit: 4096 x 4096 at 40 % 8.26 -> 7.72 us, 5120 x 5120 at 30 %
-    // 9.47 -> 9.02); a wider x holds the barrier up by itself, and the residual set is better under way (4096 x 11008,
-    // four pieces: 15.49 -> 15.57).
-    constexpr bool residual_late = TM != 0 && !BATCH && (NB > 1 ? NB > 2 || TM > 1 : VW == 2 || K < 4);
+    // 4-bit 6.75 -> 6.27 us, FP32 4096 x 4096, 4-bit 8.18 -> 7.51).  FP32 values,
+    // one vector: the same with two or more block sets where x comes with two pieces per thread (8-bit: 5120 x 5120 at 30 %
+    // 8.67 -> 8.19 us, 2048 x 5120 at 40 % 7.68 -> 7.45); with one set the other way round (4-bit: 11008 x 4096 14.71 against
+    // 15.12, 16384 x 2048 11.52 against 12.09, 8-bit 16384 x 4096 at 25 % 14.23 against 14.76; ten 256 x 512 in one launch 3.50
+    // against 3.88), and a wider x holds the barrier up by itself, so that the residual set is better under way (4096 x
+    // 11008, four pieces: 15.49 against 15.57).
+    constexpr bool residual_late = TM != 0 && !BATCH && (NB > 1 ? NB > 2 || TM > 1 : VW == 2 || (K < 4 && TM > 1));
     const uint4 *p4 = reinterpret_cast<const uint4 *>(panel);
     const uint32_t nmeta = meta_stride / 16u;
     const uint32_t nvec = n / 8u;
