@@ -57,31 +57,48 @@ int lds_limit(int *bytes)
 }
 
 // Workgroup size of a launch of `grid` workgroups in all that have `chunks` chunks between them (a wavefront takes one at
-// a time); `pieces`: 16-byte pieces of tables and x the widest of them brings to LDS; `sets`: the coarsest block set is
-// the `sets`-th.  Measured, cold, 256 panels unless said otherwise, us with 512 / 768 / 1024 threads:
-//   alone, up to 24 chunks: eight wavefronts are up and past the first barrier sooner, and two or three rounds are enough:
-//     2048 x 2048 at 30 % (10 chunks, 128 panels) 3.28 / 3.19 / 3.58, 3072 x 3072 at 40 %, 8-bit (22) 4.20 / 4.53 / 4.55,
+// a time); `pieces`: 16-byte pieces of tables and x the widest of them brings to LDS; `rows`: rows of the tallest panel (16
+// threads add up one); `sets`: the coarsest block set is the `sets`-th.  Measured, us with 512 / 768 / 1024 threads, 256 panels
+// of 16 to 20 rows unless said otherwise, launches inside a graph over three matrices in turn:
+//   alone, up to 16 chunks: eight wavefronts are up and past the first barrier sooner, and two rounds are enough, also for tall
+//     panels: 4096 x 4096 at 20 %, 4-bit (13 chunks) 4.11 / 4.08 / 4.38, 16384 x 512 at 20 % (7, 64 rows) 3.43 / 3.53 / 3.88,
 //     768 x 768 (8, 48 panels) 2.76 / 3.19 / 3.07;
-//   up to 48, images with block sets: twelve wavefronts, 4096 x 4096 at 50 %, 4-bit (43) 6.38 / 5.90 / 6.18, 8-bit (44)
-//     6.53 / 6.54 / 6.85 (launches from the host one after the other: 6.06 against 6.30 with sixteen); but with two sets (2-
-//     and 4-grained) a wavefront requests up to four chunks before it computes, and sixteen have all of them on the way
-//     at once: 5120 x 5120, 8-bit (45) 6.58 / 6.33 / 5.82; and without sets, launched from the host, seven products of a 13B
-//     layer, four of them 5120 x 5120 (30), take 52.03 us with twelve for those four and 51.83 with sixteen;
+//   up to 24, without block sets twelve: 4096 x 4096 at 35 % (23) 4.79 / 4.54 / 4.81, 1984 x 6558 at 18 % (20, 124 panels) 4.62 / 4.24 /
+//     4.37, 8192 x 2048 at 30 % (20, 32 rows) 4.63 / 4.32 / 4.58, 17216 x 1186 at 20 % (17, 67 rows) 5.05 / 4.54 / 4.62; FP32 values
+//     eight but for the tallest, 1216 x 6080 at 18 % (18, 76 panels) 3.76 / 4.07 / 4.09, 10240 x 2048 at 25 % (21, 40 rows) 5.58 / 5.58 /
+//     5.83, 17216 x 1186 5.62 / 4.94 / 5.59;
+//   up to 24, with block sets eight: 7168 x 2048 at 22 %, 8-bit (17, 28 rows) 4.01 / 4.39 / 4.68, 3776 x 3776 at 25 %, 8-bit (23) 4.12 /
+//     4.32 / 4.47; taller with one set twelve: 8192 x 2048 at 22 % (20, 32 rows) 4.52 / 4.36 / 4.68; with two sets eight all the
+//     same: 16384 x 512 at 50 % (21, 64 rows) 4.47 / 4.83 / 4.85;
+//   up to 48, one block set or an 8-grained one: twelve, 4096 x 4096 at 50 %, 4-bit (44) 6.43 / 5.96 / 6.27, 3072 x 3072 at 50 %,
+//     8-bit, 8-grained (33) 5.48 / 5.43 / 6.22, 10240 x 2048 at 25 %, 8-bit (30, 40 rows) 5.46 / 5.03 / 5.30; sixteen where more
+//     than 40 rows keep all of them in the sums: 10304 x 1858 at 35 % (26, 41 rows) 6.11 / 5.76 / 5.67, 17216 x 1186 at 30 %, 8-bit (33,
+//     67 rows) 5.82 / 5.77 / 5.32 (but 18240 x 3584 at 11 %, 29 chunks, 72 rows, 6.66 / 6.12 / 6.37); and sixteen with two sets
+//     (2- and 4-grained), where a wavefront requests up to four chunks before it computes, and sixteen have all of them on
+//     the way at once: 5120 x 5120 at 30 %, 8-bit (45) 6.54 / 6.30 / 5.85;
+//   up to 48 without block sets: sixteen.  Twelve are faster in a launch over and over, 5120 x 5120 at 30 %, 4-bit (30) 5.96 / 5.52 /
+//     5.84 (cold 6.05 / 5.71 / 5.90), but among the seven products of a decoder layer, launched from the host, four such
+//     took 52.03 us in all with twelve and 51.83 with sixteen;
 //   beyond, sixteen: 11008 x 4096 at 40 %, 4-bit (72) 10.27 / 10.06 / 9.48.
 //   Several matrices, 256 / 512 threads: small panels want more workgroups on a compute unit (its 2048 threads are eight
 //     workgroups of 256), 16 x 1024 x 1024 (7 chunks, 1024 workgroups) 5.08 / 5.97, 3 x 3072 x 3072 (15, 768) 7.00 / 7.19;
 //     larger ones, or few of them, want more wavefronts: 16 x 512 x 5120 (24, 512) 8.05 / 7.23, 3 x 768 x 768 (8, 144) 3.79 / 3.52;
 //     with an 8-grained set a kernel takes 80 registers, and a compute unit holds three workgroups of 512 but seven of 256:
 //     16 x 1024 x 4096 at 50 %, 8-bit, 128 panels (22, 2048) 17.94 / 21.55, 8 x 4096 x 4096 (44, 2048) 30.73 / 31.95.
-// Never so few threads that x takes more than the four pieces per thread that travel together: 512 x 20480 (17 chunks,
-//   2630 pieces) 5.12 / 4.66 / 5.15.
-uint32_t choose_threads(uint32_t grid, uint64_t chunks, uint32_t pieces, bool alone, uint32_t sets)
+// The size then grows, up to 1024 alone and 512 among several, until the four pieces per thread that travel together bring
+//   all of x: 512 x 20480 (17 chunks, 2630 pieces) 5.12 / 4.66 / 5.15.
+uint32_t choose_threads(uint32_t grid, uint64_t chunks, uint32_t pieces, uint32_t rows, bool fp32, bool alone, uint32_t sets)
 {
+    auto up_to = [&](uint64_t per_panel) { return chunks <= per_panel * grid; };
     uint32_t t;
-    if (alone)
-        t = chunks <= 24u * (uint64_t)grid ? 512u : chunks <= 48u * (uint64_t)grid && (sets == 1u || sets >= 3u) ? 768u : 1024u;
-    else
-        t = (chunks <= 16u * (uint64_t)grid && grid >= 448u) || (sets >= 3u && grid >= 1024u) ? 256u : 512u;
+    if (alone) {
+        t = 1024u;
+        if (sets == 0u ? up_to(24) : sets != 2u && up_to(48) && rows <= 40u) t = 768u;
+        const bool short_panels = sets == 0u ? fp32 && rows <= 48u : sets == 2u || rows <= 28u;
+        if (up_to(16) || (up_to(24) && short_panels)) t = 512u;
+    } else {
+        t = (up_to(16) && grid >= 448u) || (sets >= 3u && grid >= 1024u) ? 256u : 512u;
+    }
     while (pieces > 4u * t && t < (alone ? 1024u : 512u)) t += 256u;
     return t;
 }
@@ -357,7 +374,7 @@ int ecspmv_run_batch(const ecspmv_matrix *const *As, const void *const *d_xs, vo
         ecs::EcsBatch b;
         std::memset(&b, 0, offsetof(ecs::EcsBatch, item) + sizeof(ecs::EcsBatchItem) * (size_t)(nb == 1 ? 1 : ECS_MAX_BATCH));
         b.count = (uint32_t)nb;
-        uint32_t blocks = 0, lds = 0, mask = 0, pieces = 0;
+        uint32_t blocks = 0, lds = 0, mask = 0, pieces = 0, rows = 0;
         uint64_t chunks = 0;
         for (int32_t i = 0; i < nb; ++i) {
             const int32_t src = base + i;
@@ -376,8 +393,10 @@ int ecspmv_run_batch(const ecspmv_matrix *const *As, const void *const *d_xs, vo
             mask |= im.type_mask;
             chunks += im.total_chunks;
             pieces = std::max(pieces, (im.meta_stride + it.x_bytes) / 16u);
+            rows = std::max(rows, (uint32_t)((im.m + im.num_panels - 1) / im.num_panels));
         }
-        uint32_t threads = choose_threads(blocks, chunks, pieces, nb == 1, mask >= 8u ? 4u : mask >= 4u ? 3u : mask >= 2u ? 2u : mask);
+        uint32_t threads = choose_threads(blocks, chunks, pieces, rows, vbits == 32, nb == 1,
+                                          mask >= 8u ? 4u : mask >= 4u ? 3u : mask >= 2u ? 2u : mask);
         for (int32_t i = 0; i < nb; ++i) {
             const int t = As[base + i]->image.threads_per_wg;
             if (t) threads = (uint32_t)t;                      // a build-time choice overrides
