@@ -80,11 +80,17 @@ int lds_limit(int *bytes)
 //     5.84 (cold 6.05 / 5.71 / 5.90), but among the seven products of a decoder layer, launched from the host, four such
 //     took 52.03 us in all with twelve and 51.83 with sixteen;
 //   beyond, sixteen: 11008 x 4096 at 40 %, 4-bit (72) 10.27 / 10.06 / 9.48.
-//   Several matrices, 256 / 512 threads: small panels want more workgroups on a compute unit (its 2048 threads are eight
-//     workgroups of 256), 16 x 1024 x 1024 (7 chunks, 1024 workgroups) 5.08 / 5.97, 3 x 3072 x 3072 (15, 768) 7.00 / 7.19;
-//     larger ones, or few of them, want more wavefronts: 16 x 512 x 5120 (24, 512) 8.05 / 7.23, 3 x 768 x 768 (8, 144) 3.79 / 3.52;
-//     with an 8-grained set a kernel takes 80 registers, and a compute unit holds three workgroups of 512 but seven of 256:
-//     16 x 1024 x 4096 at 50 %, 8-bit, 128 panels (22, 2048) 17.94 / 21.55, 8 x 4096 x 4096 (44, 2048) 30.73 / 31.95.
+//   Several matrices, 256 / 512 threads: with up to 16 chunks a panel 256, where the launch is more than a compute unit holds
+//     at 512 threads (2048 threads each: 1024 workgroups), 5 x 4096 x 4096 at 15 % (11 chunks, 1280 workgroups) 8.65 / 8.97, 5 x
+//     16384 x 512 (7, 1280, 64 rows) 7.29 / 8.62, FP32 values from 768 on, 3 x 4096 x 4096 at 15 % (768) 8.26 / 8.72; or where
+//     there is more than one workgroup for a compute unit, a thread brings one piece (FP32: two) and 16 lanes a row or little
+//     more: 16 x 512 x 512 (3, 512) 3.94 / 4.44, 6 x 768 x 768 (8, 288) 4.24 / 4.50, FP32 4.80 / 5.73, 5 x 1024 x 1024 (5, 320)
+//     3.80 / 3.93, 3 x 5120 x 1024 (4, 768, 20 rows) 4.62 / 4.70; one for each: 8 x 512 x 512 (3, 256) 3.68 / 3.67, 3 x 1024 x 1024
+//     (5, 192) 3.67 / 3.43.  Larger panels, wider x or taller panels want more wavefronts: 16 x 512 x 5120 (24, 512) 8.05 / 7.23,
+//     2 x 4096 x 4096 at 20 % (13, 512) 6.10 / 5.59, 3 x 3562 x 3562 (8, 666) 5.96 / 5.68, 3 x 6144 x 1024 (5, 768, 24 rows) 4.85 /
+//     4.80, 3 x 16384 x 512, 8-bit (11, 768, 64 rows) 7.72 / 7.02.  With an 8-grained set a kernel takes 80 registers, and a compute
+//     unit holds three workgroups of 512 but seven of 256: 16 x 1024 x 4096 at 50 %, 8-bit, 128 panels each (22, 2048) 17.94 / 21.55,
+//     5 x 4096 x 4096 (44, 1280) 20.56 / 21.27; 6 x 8192 x 2048 at 60 % (47, 1536, 32 rows) 27.73 / 27.59.
 // The size then grows, up to 1024 alone and 512 among several, until the four pieces per thread that travel together bring
 //   all of x: 512 x 20480 (17 chunks, 2630 pieces) 5.12 / 4.66 / 5.15.
 uint32_t choose_threads(uint32_t grid, uint64_t chunks, uint32_t pieces, uint32_t rows, bool fp32, bool alone, uint32_t sets)
@@ -97,7 +103,8 @@ uint32_t choose_threads(uint32_t grid, uint64_t chunks, uint32_t pieces, uint32_
         const bool short_panels = sets == 0u ? fp32 && rows <= 48u : sets == 2u || rows <= 28u;
         if (up_to(16) || (up_to(24) && short_panels)) t = 512u;
     } else {
-        t = (up_to(16) && grid >= 448u) || (sets >= 3u && grid >= 1024u) ? 256u : 512u;
+        const bool crowded = grid > (fp32 ? 767u : 1024u), light = grid > 256u && pieces <= (fp32 ? 512u : 256u) && rows <= 20u;
+        t = (up_to(16) && (crowded || light)) || (sets >= 3u && grid >= 1024u) ? 256u : 512u;
     }
     while (pieces > 4u * t && t < (alone ? 1024u : 512u)) t += 256u;
     return t;

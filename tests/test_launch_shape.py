@@ -62,9 +62,26 @@ ALONE = [
     case(1024, 4, 40000, 0.02, (1, 15.5), pieces=(3073, 9999)),
     case(448, 16, 4000, 0.2, (8, 15.5), fixed=448),              # the caller's choice stands
 ]
+SEVERAL = [
+    case(512, 16, 900, 0.3, (2, 15.5), panels=50, count=5, pieces=(1, 256)),                       # 250 workgroups
+    case(256, 16, 900, 0.3, (2, 15.5), panels=54, count=5, pieces=(1, 256)),                       # 270
+    case(512, 24, 900, 0.3, (2, 15.5), panels=54, count=5, pieces=(1, 256)),                       # taller panels
+    case(512, 16, 2400, 0.1, (2, 15.5), panels=54, count=5, pieces=(257, 512)),                    # a wider x
+    case(256, 16, 1200, 0.2, (2, 15.5), panels=54, count=5, fp32=True, pieces=(257, 512)),
+    case(512, 16, 2400, 0.1, (2, 15.5), panels=54, count=5, fp32=True, pieces=(513, 1024)),
+    case(512, 16, 2400, 0.1, (2, 15.5), panels=128, count=8, pieces=(257, 512)),                   # 1024
+    case(256, 24, 2400, 0.1, (2, 15.5), panels=129, count=8, pieces=(257, 512)),                   # 1032
+    case(512, 24, 2400, 0.1, (2, 15.5), panels=96, count=7, fp32=True, pieces=(513, 1024)),        # 672
+    case(256, 24, 2400, 0.1, (2, 15.5), panels=96, count=8, fp32=True, pieces=(513, 1024)),        # 768
+    case(512, 16, 2400, 0.5, (17, 40), panels=129, count=8, pieces=(257, 1024)),
+    case(256, 16, 2400, 0.4, (17, 40), g=8, flags=4, panels=64, count=16, pieces=(257, 1024)),     # 1024, 8-grained
+    case(512, 16, 2400, 0.4, (17, 40), g=8, flags=4, panels=63, count=16, pieces=(257, 1024)),     # 1008
+    case(512, 16, 2400, 0.4, (17, 40), g=4, panels=64, count=16, pieces=(257, 1024)),
+    case(512, 4, 20480, 0.02, (1, 15.5), panels=65, count=16, pieces=(2049, 3072)),                # 512 at most
+]
 
 
-@pytest.mark.parametrize("cases", [ALONE], ids=["alone"])
+@pytest.mark.parametrize("cases", [ALONE, SEVERAL], ids=["alone", "several"])
 def test_workgroup_size(tmp_path, cases):
     for c, got in zip(cases, standin.run(tmp_path, CHILD, cases)):
         assert c["chunks"][0] <= got["chunks"] <= c["chunks"][1], (c, got)           # the case is what it says
