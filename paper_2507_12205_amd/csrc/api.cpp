@@ -436,10 +436,15 @@ int ecspmv_run_multi(const ecspmv_matrix *A, const void *d_X, void *d_Y, int32_t
     int lim = 0;
     int e = lds_limit(&lim);
     if (e) return hip_status(e);
-    // Small panels: eight wavefronts, as with one vector (768 x 768, eight right-hand sides, 8 chunks per panel: 4.50 us with
-    // 1024 threads, 4.04 with 512; 2048 x 2048 at 30 %, 10 chunks: 5.30 and 4.95); larger ones sixteen (5120 x 5120, two,
-    // 30 chunks: 6.55 and 6.96).
-    const bool small = im.total_chunks <= 12u * (uint64_t)im.num_panels;
+    // Small panels: eight wavefronts, as with one vector, us with 512 / 1024 threads: up to 12 chunks a panel (768 x 768, eight
+    // right-hand sides, 8 chunks: 4.04 / 4.50; 16384 x 512, 7 chunks, four: 3.98 / 4.52), with two right-hand sides up to 20
+    // (FP32 2048 x 2048 at 30 %, 8-bit, 15 chunks: 4.22 / 5.26; 2048 x 8192 at 12 %, 18: 4.20 / 4.46; 16384 x 1024 at 25 %, 17:
+    // 5.12 / 5.24; four, 2048 x 4096 at 25 %, 16: 5.29 / 5.11); but not with more X than they bring well (up to 12 chunks 64 KB:
+    // FP32, eight, 1024 x 4096 at 15 %, 11 chunks, 128 KB: 7.89 / 7.39; up to 20 chunks 32 KB: FP32, two, 1408 x 6144 at 17 %, 17
+    // chunks, 48 KB: 5.69 / 5.53).  Larger ones sixteen (5120 x 5120, two, 30 chunks: 6.96 / 6.55).
+    const uint64_t all_x = (uint64_t)im.n * vw * (uint32_t)nb;
+    auto up_to = [&](uint64_t per_panel) { return im.total_chunks <= per_panel * (uint64_t)im.num_panels; };
+    const bool small = (up_to(12) && all_x <= 65536u) || (nb == 2 && up_to(20) && all_x <= 32768u);
     const uint32_t threads = im.threads_per_wg ? (uint32_t)im.threads_per_wg : small ? 512u : 1024u, waves = threads / 64u;
     // `per` columns of X and their partial sums sit in the LDS of a workgroup, so a panel takes nb / per workgroups, all
     // of one launch.  Where the partial sums of a whole panel do not fit beside X, the residual chunks are taken in

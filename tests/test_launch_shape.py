@@ -79,9 +79,20 @@ SEVERAL = [
     case(512, 16, 2400, 0.4, (17, 40), g=4, panels=64, count=16, pieces=(257, 1024)),
     case(512, 4, 20480, 0.02, (1, 15.5), panels=65, count=16, pieces=(2049, 3072)),                # 512 at most
 ]
+MULTI = [
+    case(512, 16, 2000, 0.2, (4, 11.5), nb=8),
+    case(1024, 16, 2000, 0.4, (12.5, 19.5), nb=4),
+    case(512, 16, 2000, 0.4, (12.5, 19.5), nb=2),
+    case(1024, 16, 2000, 0.8, (21, 30), nb=2),
+    case(512, 16, 4096, 0.1, (4, 11.5), nb=8),                                                     # 64 KB of X
+    case(1024, 16, 4097, 0.1, (4, 11.5), nb=8),
+    case(1024, 16, 2400, 0.1, (4, 11.5), nb=8, fp32=True),
+    case(512, 16, 4096, 0.2, (12.5, 19.5), nb=2, fp32=True),                                       # 32 KB
+    case(1024, 16, 4097, 0.2, (12.5, 19.5), nb=2, fp32=True),
+]
 
 
-@pytest.mark.parametrize("cases", [ALONE, SEVERAL], ids=["alone", "several"])
+@pytest.mark.parametrize("cases", [ALONE, SEVERAL, MULTI], ids=["alone", "several", "multi"])
 def test_workgroup_size(tmp_path, cases):
     for c, got in zip(cases, standin.run(tmp_path, CHILD, cases)):
         assert c["chunks"][0] <= got["chunks"] <= c["chunks"][1], (c, got)           # the case is what it says
