@@ -284,38 +284,42 @@ __device__ __forceinline__ void compute_unit(const Ctx &c, const uint16_t *utab,
     XWords<NB, VW> xv[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) xv[k].read(c.xs, start + rel[k]);
-    float acc[G][NB];
-#pragma unroll
-    for (int q = 0; q < G; ++q)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[q][b] = 0.0f;
-#pragma unroll
-    for (int f = 0; f < 4 * G; ++f) {                              // f = column * G + row
-        if constexpr (VW == 2) {
-            const uint4 q = r.v[f >> 3];
-            const uint32_t word = ((f >> 1) & 3) == 0 ? q.x : ((f >> 1) & 3) == 1 ? q.y : ((f >> 1) & 3) == 2 ? q.z : q.w;
-            const uint32_t hb = (f & 1) ? (word >> 16) : (word & 0xFFFF);
-#pragma unroll
-            for (int b = 0; b < NB; ++b) acc[f % G][b] = fma_h(hb, xv[f / G].get(b), acc[f % G][b]);
-        } else {
-            const uint4 q = r.v[f >> 2];
-            const uint32_t word = (f & 3) == 0 ? q.x : (f & 3) == 1 ? q.y : (f & 3) == 2 ? q.z : q.w;
-#pragma unroll
-            for (int b = 0; b < NB; ++b) acc[f % G][b] = fmaf(__uint_as_float(word), xv[f / G].get(b), acc[f % G][b]);
-        }
-    }
+    // Several right-hand sides: up to four columns of X at a time, as their sums lie in LDS, so that no more than 4 G sums are
+    // held at once (eight columns of an 8-grained set took 128 registers and 112 bytes of scratch per lane).  The words of W
+    // are made opaque in between: the compiler would otherwise keep all 4 G converted values for the next columns.
     typedef Partial<NB> P;
+    uint32_t w[G * VW];
+#pragma unroll
+    for (int k = 0; k < G * VW / 4; ++k) w[4 * k] = r.v[k].x, w[4 * k + 1] = r.v[k].y, w[4 * k + 2] = r.v[k].z, w[4 * k + 3] = r.v[k].w;
 #pragma unroll
     for (int p = 0; p < NB / P::G; ++p) {
+        if (p) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < G * VW; ++k) asm volatile("" : "+v"(w[k]));
+        }
+        float acc[G][P::G];
+#pragma unroll
+        for (int q = 0; q < G; ++q)
+#pragma unroll
+            for (int k = 0; k < P::G; ++k) acc[q][k] = 0.0f;
+#pragma unroll
+        for (int f = 0; f < 4 * G; ++f) {                          // f = column of W * G + row
+            const uint32_t bits = VW == 4 ? w[f] : (f & 1) ? w[f >> 1] >> 16 : w[f >> 1] & 0xFFFFu;
+#pragma unroll
+            for (int k = 0; k < P::G; ++k) {
+                const float x = xv[f / G].get(p * P::G + k);
+                acc[f % G][k] = VW == 2 ? fma_h(bits, x, acc[f % G][k]) : fmaf(__uint_as_float(bits), x, acc[f % G][k]);
+            }
+        }
         typename P::vec t;
 #pragma unroll
         for (int k = 0; k < P::G; ++k) {
-            const int b = p * P::G + k;
 #pragma unroll
-            for (int q = 0; q < G; ++q) acc[q][b] = row16_allreduce(acc[q][b]);
-            float out = acc[0][b];
+            for (int q = 0; q < G; ++q) acc[q][k] = row16_allreduce(acc[q][k]);
+            float out = acc[0][k];
 #pragma unroll
-            for (int q = 1; q < G; ++q) out = (j == (uint32_t)q) ? acc[q][b] : out;
+            for (int q = 1; q < G; ++q) out = (j == (uint32_t)q) ? acc[q][k] : out;
             t[k] = out;
         }
         if (active && j < (uint32_t)G) reinterpret_cast<typename P::vec *>(c.slots)[ue[1 + j] + p * c.pstride] = t;
@@ -896,9 +900,12 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     __syncthreads();
     ECS_STAMP(c, 4);            // first barrier passed
 
-    if constexpr (residual_late) rs.prologue(c, hdr, dealt);
+    // (eight right-hand sides and an 8-grained set: after that set's first chunk, whose sums leave no registers for it)
+    constexpr bool residual_last = NB == 8 && (TM & 4) != 0;
+    if constexpr (residual_late && !residual_last) rs.prologue(c, hdr, dealt);
     if constexpr ((TM & 8) != 0) b16.run_first(c);
     if constexpr ((TM & 4) != 0) b8.run_first(c);
+    if constexpr (residual_late && residual_last) rs.prologue(c, hdr, dealt);
     if constexpr ((TM & 2) != 0) b4.run_first(c);
     if constexpr ((TM & 1) != 0) b2.run_first(c);
     if constexpr ((TM & 8) != 0) b16.run(c);
