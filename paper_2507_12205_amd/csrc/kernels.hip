@@ -762,13 +762,17 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // wavefronts has its header 1.4 us after the workgroup started, against 0.5 us this way).
     // (Measured and not kept: only the first four wavefronts staging all pieces.  The first barrier then passes 0.7 us
     // earlier, but those wavefronts request their chunks later, and when the chunks are requested is what decides.)
-    // buffers per set: deeper where chunks are small and frequent, shallower where registers run out
-    constexpr bool wide = (TM & 12) != 0;
+    // buffers per set: deeper where chunks are small and frequent, shallower where registers run out.  Four right-hand sides
+    // with 2- and 4-grained sets are kept at 64 VGPRs, so that two workgroups of 1024 threads share a compute unit where LDS
+    // allows (20480 x 1024 at 50 %, 8-bit, in 512 panels: 9.1 us, with 71 VGPRs 10.8; in 256 panels 4096 x 11008 at 40 % 13.8
+    // against 14.3): one buffer for the 2-grained set, two pieces at a time in the staging loop, and the residual set
+    // requested after the first 4-grained chunk.
+    constexpr bool wide = (TM & 12) != 0, tight = NB == 4 && VW == 2 && TM == 3;
     constexpr bool straight = !BATCH;
     BlockSet<16, DB, 1, NB, VW, straight> b16;
     BlockSet<8, DB, 1, NB, VW, straight> b8;
     BlockSet<4, DB, wide ? 1 : D4, NB, VW, straight> b4;
-    BlockSet<2, DB, wide ? 2 : D2, NB, VW, straight> b2;
+    BlockSet<2, DB, wide ? 2 : tight ? 1 : D2, NB, VW, straight> b2;
     ResidualSet<DB, (NB > 1) ? 1 : wide ? 2 : (TM == 0 && BATCH ? DR0B : DR), TM == 0 && BATCH, NB, VW> rs;
     // A launch of an image with block sets that shares its compute units with few others requests the residual set's
     // first chunks only after the barrier: a wavefront cannot pass the barrier before its requests are out, with every
@@ -857,7 +861,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // FP32 sixteen 1000 x 10000 16.5 -> 18.7.  A launch of one matrix has more threads and hardly ever gets here: one at
     // a time, the code around it is then 1 % faster (5120 x 20480 10.90 -> 10.79).
     if constexpr (K == 4) {
-        constexpr uint32_t U = NB == 1 ? (LONE ? 1 : 2) : NB == 2 || NB * VW >= 32 ? 1 : 4;
+        constexpr uint32_t U = NB == 1 ? (LONE ? 1 : 2) : NB == 2 || NB * VW >= 32 ? 1 : tight ? 2 : 4;
         for (uint32_t idx = tid + (uint32_t)K * nt; idx < ntot; idx += U * nt) {
             uint4 t[U];
 #pragma unroll
@@ -900,13 +904,15 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     __syncthreads();
     ECS_STAMP(c, 4);            // first barrier passed
 
-    // (eight right-hand sides and an 8-grained set: after that set's first chunk, whose sums leave no registers for it)
-    constexpr bool residual_last = NB == 8 && (TM & 4) != 0;
-    if constexpr (residual_late && !residual_last) rs.prologue(c, hdr, dealt);
+    // (eight right-hand sides with an 8-grained set, and `tight`: after the first chunk of the coarsest set, whose sums leave no
+    // registers for it)
+    constexpr bool after_b8 = NB == 8 && (TM & 4) != 0;
+    if constexpr (residual_late && !after_b8 && !tight) rs.prologue(c, hdr, dealt);
     if constexpr ((TM & 8) != 0) b16.run_first(c);
     if constexpr ((TM & 4) != 0) b8.run_first(c);
-    if constexpr (residual_late && residual_last) rs.prologue(c, hdr, dealt);
+    if constexpr (residual_late && after_b8) rs.prologue(c, hdr, dealt);
     if constexpr ((TM & 2) != 0) b4.run_first(c);
+    if constexpr (residual_late && tight) rs.prologue(c, hdr, dealt);
     if constexpr ((TM & 1) != 0) b2.run_first(c);
     if constexpr ((TM & 8) != 0) b16.run(c);
     if constexpr ((TM & 4) != 0) b8.run(c);

@@ -56,5 +56,5 @@ def test_two_workgroups_of_1024_threads(table):
     """64 VGPRs: 32 wavefronts on a compute unit.  One vector in FP16 with up to 4-grained sets, and several where LDS can
     hold two panels (launches in phases fill it)."""
     over = {k: v for k, v in table.items() if k[5] == 2 and k[2] != 3 and v[0] > 64
-            and k[0] <= {1: 3, 2: 3, 4: 1, 8: 1}[k[4]]}
+            and k[0] <= {1: 3, 2: 3, 4: 3, 8: 1}[k[4]]}
     assert not over, over
