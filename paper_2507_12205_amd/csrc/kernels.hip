@@ -1244,8 +1244,10 @@ static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes
     // index compression switched off (absolute 16-bit columns): the ablation point, one variant per set mask
     if (delta_bits == 16) return launch_k<TM, 16, false, 4, 1>(batch, threads, lds_bytes, stream);
     // Residual-only images and images with one block set have a second variant for launches that carry several
-    // SpMVs.  The residual-only one (deeper buffers) pays once more than three 512-thread workgroups per compute
-    // unit are launched (measured at 2, 3 and 7 per compute unit: slower, 1 % slower, faster).
+    // SpMVs.  The residual-only one (deeper buffers) was measured at 2, 3 and 7 512-thread workgroups per compute unit: slower,
+    // 1 % slower, faster.  Around the line of 768 workgroups it gains little or loses, us with shallow / deep buffers: 256
+    // threads 12 x 1024 x 1024 at 30 % (768) 4.30 / 4.28, 13 of them (832) 4.59 / 4.50, 12 x 1408 x 597 at 20 % (1056) 4.01 / 4.31;
+    // 512 threads 3 x 4096 x 4096 at 20 % (768) 6.49 / 6.77, four (1024) 7.85 / 8.40, 4 x 5120 x 5120 at 30 % (1024) 14.05 / 14.22.
     const uint32_t grid = batch.item[batch.count - 1].block_end;
     if ((TM == 0 && batch.count > 1 && grid > 768) || (TM == 1 && batch.count > 1))
         return delta_bits == 4 ? launch_b<TM, 4, TM <= 1>(batch, threads, lds_bytes, stream)

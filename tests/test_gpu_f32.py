@@ -191,7 +191,7 @@ def test_several_right_hand_sides(E, nb, bits):
 
 def test_several_right_hand_sides_split_and_refused(E):
     import torch
-    # 4 * n * nb bytes of X exceed LDS: two or four launches with a row stride, aligned and not
+    # 4 * n * nb bytes of X exceed LDS: two or four workgroups per panel with a row stride, aligned and not
     for (m, n, nb) in ((64, 9000, 8), (48, 15000, 4)):
         W = make_f32(gen.small_random(m, n, 0.05, 5 + nb)[0], 9)
         A = check_multi(E, W, nb, f"split {m}x{n}", delta_bits=4, max_granularity=2)

@@ -109,13 +109,13 @@ def test_full_size_projection(E):
 
 
 def test_columns_split_over_launches(E):
-    """X too wide for LDS: the call runs as several launches of nb / 2 or nb / 4 right-hand sides, each reading its
-    columns of X and writing its columns of Y with the row stride nb.  Same band, same bits per column."""
+    """X too wide for LDS: a panel takes two or four workgroups of one launch with nb / 2 or nb / 4 right-hand sides each,
+    which read their columns of X and write their columns of Y with the row stride nb.  Same band, same bits per column."""
     for (m, n, nb) in ((96, 12000, 8), (64, 30000, 4), (64, 30000, 8), (40, 13824, 8)):
         W, _ = gen.small_random(m, n, 0.05, 11 + nb)
         A = check(E, W, nb, f"split {m}x{n}", delta_bits=4, max_granularity=2)
         check(E, W, nb, f"split {m}x{n}, X two bytes off a 16-byte boundary", x_offset=1, delta_bits=4, max_granularity=2)
-        assert 2 * n * nb + A.ecspmv_stats().meta_stride > 160 * 1024         # it could not have run as one launch
+        assert 2 * n * nb + A.ecspmv_stats().meta_stride > 160 * 1024         # one workgroup could not have held all of X
 
 
 def test_refusals(E):
