@@ -57,9 +57,10 @@ int lds_limit(int *bytes)
 }
 
 // Workgroup size of a launch of `grid` workgroups in all that have `chunks` chunks between them (a wavefront takes one at
-// a time); `pieces`: 16-byte pieces of tables and x the widest of them brings to LDS; `rows`: rows of the tallest panel (16
-// threads add up one); `sets`: the coarsest block set is the `sets`-th.  Measured, us with 512 / 768 / 1024 threads, 256 panels
-// of 16 to 20 rows unless said otherwise, launches inside a graph over three matrices in turn:
+// a time); `pieces`: 16-byte pieces of tables and x the widest of them brings to LDS; `rows`: rows of a panel
+// on average, the most of all matrices (16 threads add up one); `sets`: the coarsest block set is the `sets`-th.  Measured, us
+// with 512 / 768 / 1024 threads, 256 panels of 16 to 20 rows unless said otherwise, launches inside a graph over three matrices
+// in turn:
 //   alone, up to 16 chunks: eight wavefronts are up and past the first barrier sooner, and two rounds are enough, also for tall
 //     panels: 4096 x 4096 at 20 %, 4-bit (13 chunks) 4.11 / 4.08 / 4.38, 16384 x 512 at 20 % (7, 64 rows) 3.43 / 3.53 / 3.88,
 //     768 x 768 (8, 48 panels) 2.76 / 3.19 / 3.07;
