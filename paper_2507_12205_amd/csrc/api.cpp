@@ -149,7 +149,7 @@ int parse_opts(const ecspmv_build_opts *o, ecs::BuildParams &bp, int value_bits 
     return ECSPMV_OK;
 }
 
-int finish_build(const ecs::Csr &A, const ecs::BuildParams &bp, ecspmv_matrix **out)
+int finish_build(const ecs::Source &A, const ecs::BuildParams &bp, ecspmv_matrix **out)
 {
     ecspmv_matrix *h = new (std::nothrow) ecspmv_matrix;
     if (!h) return ECSPMV_ERR_NOMEM;
@@ -209,9 +209,7 @@ int ecspmv_build_dense(const uint16_t *W, int64_t m, int64_t n, int64_t ld, cons
     int s = parse_opts(opts, bp);
     if (s) return s;
     try {
-        ecs::Csr A;
-        ecs::csr_from_dense(W, m, n, ld, bp.num_threads, A);
-        return finish_build(A, bp, out);
+        return finish_build({m, n, 16, W, ld, nullptr}, bp, out);
     } catch (const std::bad_alloc &) {
         return ECSPMV_ERR_NOMEM;
     } catch (...) {                                  // nothing may leave through the C ABI (a worker thread that could
@@ -231,7 +229,7 @@ int ecspmv_build_csr(const int64_t *rowptr, const int32_t *col, const uint16_t *
     try {
         ecs::Csr A;
         if (ecs::csr_from_csr(rowptr, col, val, m, n, A)) return ECSPMV_ERR_INVALID;
-        return finish_build(A, bp, out);
+        return finish_build({m, n, 16, nullptr, 0, &A}, bp, out);
     } catch (const std::bad_alloc &) {
         return ECSPMV_ERR_NOMEM;
     } catch (...) {                                  // nothing may leave through the C ABI (a worker thread that could
@@ -248,9 +246,7 @@ int ecspmv_build_dense_f32(const float *W, int64_t m, int64_t n, int64_t ld, con
     int s = parse_opts(opts, bp, 32);
     if (s) return s;
     try {
-        ecs::Csr A;
-        ecs::csr_from_dense_f32(reinterpret_cast<const uint32_t *>(W), m, n, ld, bp.num_threads, A);
-        return finish_build(A, bp, out);
+        return finish_build({m, n, 32, W, ld, nullptr}, bp, out);
     } catch (const std::bad_alloc &) {
         return ECSPMV_ERR_NOMEM;
     } catch (...) {                                  // nothing may leave through the C ABI (a worker thread that could
@@ -270,7 +266,7 @@ int ecspmv_build_csr_f32(const int64_t *rowptr, const int32_t *col, const float 
     try {
         ecs::Csr A;
         if (ecs::csr_from_csr_f32(rowptr, col, reinterpret_cast<const uint32_t *>(val), m, n, A)) return ECSPMV_ERR_INVALID;
-        return finish_build(A, bp, out);
+        return finish_build({m, n, 32, nullptr, 0, &A}, bp, out);
     } catch (const std::bad_alloc &) {
         return ECSPMV_ERR_NOMEM;
     } catch (...) {                                  // nothing may leave through the C ABI (a worker thread that could

@@ -3,7 +3,11 @@
 #define ECSPMV_ENCODER_H
 
 #include <cstdint>
+#include <cstdlib>
+#include <new>
 #include <vector>
+
+#include <sys/mman.h>
 
 #include "../../include/ecspmv.h"
 #include "ecspmv_format.h"
@@ -17,6 +21,57 @@ struct Csr {
     std::vector<int32_t> col;
     std::vector<uint32_t> val;
 };
+
+// What an image is built from: a dense matrix (rows of n values, `ld` apart, 16 or 32 bits each), or a CSR matrix.
+struct Source {
+    int64_t m = 0, n = 0;
+    int value_bits = 16;
+    const void *dense = nullptr;
+    int64_t ld = 0;
+    const Csr *csr = nullptr;
+};
+
+// Memory that is written in full before it is read: not filled beforehand (by one thread, with every page touched twice), and
+// in huge pages where it is large (4096 x 4096 at 50 %: 22 MB of image, 5400 page faults against 11).
+template <class T>
+struct RawAllocator {
+    typedef T value_type;
+    RawAllocator() = default;
+    template <class U>
+    RawAllocator(const RawAllocator<U> &) {}
+    T *allocate(size_t n)
+    {
+        constexpr size_t kHuge = 2u << 20;
+        if (n > (size_t)-1 / 2 / sizeof(T)) throw std::bad_alloc();
+        const size_t bytes = n * sizeof(T);
+        void *p = nullptr;
+        if (bytes >= 2 * kHuge) {
+            p = std::aligned_alloc(kHuge, (bytes + kHuge - 1) / kHuge * kHuge);
+            if (p) (void)madvise(p, bytes, MADV_HUGEPAGE);                   // no more than advice
+        } else {
+            p = std::malloc(bytes);
+        }
+        if (!p) throw std::bad_alloc();
+        return static_cast<T *>(p);
+    }
+    void deallocate(T *p, size_t) { std::free(p); }
+    template <class U>
+    void construct(U *p)
+    {
+        ::new ((void *)p) U;                                                 // leaves the bytes as they are
+    }
+    template <class U, class... Args>
+    void construct(U *p, Args &&...args)
+    {
+        ::new ((void *)p) U(static_cast<Args &&>(args)...);
+    }
+    template <class U>
+    bool operator==(const RawAllocator<U> &) const { return true; }
+    template <class U>
+    bool operator!=(const RawAllocator<U> &) const { return false; }
+};
+template <class T>
+using RawVector = std::vector<T, RawAllocator<T>>;
 
 struct BuildParams {
     int delta_bits = 8;
@@ -32,7 +87,7 @@ struct BuildParams {
 };
 
 struct Image {
-    std::vector<uint8_t> bytes;
+    RawVector<uint8_t> bytes;
     int64_t m = 0, n = 0, nnz = 0;
     int num_panels = 0, threads_per_wg = 1024, delta_bits = 8, value_bits = 16;
     uint32_t panel_stride = 0, meta_stride = 0, max_slots = 0, lds_bytes = 0;
@@ -53,9 +108,8 @@ struct BlockSets {
 
 int csr_from_dense(const uint16_t *W, int64_t m, int64_t n, int64_t ld, int threads, Csr &out);
 int csr_from_csr(const int64_t *rowptr, const int32_t *col, const uint16_t *val, int64_t m, int64_t n, Csr &out);
-int csr_from_dense_f32(const uint32_t *W, int64_t m, int64_t n, int64_t ld, int threads, Csr &out);
 int csr_from_csr_f32(const int64_t *rowptr, const int32_t *col, const uint32_t *val, int64_t m, int64_t n, Csr &out);
-int build_image(const Csr &A, const BuildParams &bp, Image &out);
+int build_image(const Source &A, const BuildParams &bp, Image &out);
 int walk_image(const Image &im, Triples *tri, BlockSets *bs);
 
 }  // namespace ecs
