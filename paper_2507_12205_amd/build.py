@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
@@ -25,9 +26,11 @@ def is_stale() -> bool:
 
 
 def build_all(verbose: bool = False) -> None:
-    """The product library and the stamped one for the timeline script."""
-    build(verbose)
-    build(verbose, extra_flags=("-DECS_TRACE=1",), out=TRACE_LIB)
+    """The product library and the stamped one for the timeline script, side by side."""
+    with ThreadPoolExecutor(2) as pool:
+        jobs = [pool.submit(build, verbose), pool.submit(build, verbose, ("-DECS_TRACE=1",), TRACE_LIB)]
+    for job in jobs:
+        job.result()
 
 
 def build(verbose: bool = False, extra_flags=(), out: str = LIB) -> str:

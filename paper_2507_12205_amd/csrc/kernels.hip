@@ -817,7 +817,8 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     ECS_STAMP(c, 23);           // header requested
     uint4 s0 = *piece(0), s1 = s0, s2 = s0, s3 = s0;
     if constexpr (K > 1) s1 = *piece(1);
-    if constexpr (K > 2) s2 = *piece(2), s3 = *piece(3);
+    if constexpr (K > 2) s2 = *piece(2);
+    if constexpr (K > 3) s3 = *piece(3);
     ECS_STAMP(c, 20);           // header and first pieces requested
     __builtin_amdgcn_sched_barrier(0);      // these loads do not wait for the header: keep them ahead of those that do
 #pragma unroll
@@ -832,14 +833,22 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     }
 
     // As soon as the header is here, the first chunks of every set are requested (one per register buffer), before
-    // anything is computed and before the tables and x have even reached LDS.
+    // anything is computed and before the tables and x have even reached LDS.  With several right-hand sides only once this
+    // wavefront's part of X is in LDS: loads return in the order they were requested, so what of X comes late (a wide X, the
+    // wavefronts that start last) would queue behind everyone's chunks, and nothing is computed before all of X is there.  us, chunks
+    // first / X first: two, 5120 x 5120 at 30 %, 8-bit 6.56 / 6.21, 2048 x 8192 at 40 %, 8-bit 8.15 / 7.77, FP32 4096 x 4096 at 30 % 6.37 /
+    // 5.71; four, 5120 x 13824 at 30 % 14.38 / 13.65, FP32 4096 x 4096 7.20 / 6.62; eight, 5120 x 5120 at 30 % 9.56 / 9.05; a launch that
+    // leaves most of the chip idle the other way round, 48 panels of 768 x 768 with 8-bit deltas, two, 3.53 / 3.69.
     uint32_t dealt = 0;
+    auto request_first = [&]() {
+        if constexpr ((TM & 8) != 0) b16.prologue(c, hdr, 3, dealt);
+        if constexpr ((TM & 4) != 0) b8.prologue(c, hdr, 2, dealt);
+        if constexpr ((TM & 2) != 0) b4.prologue(c, hdr, 1, dealt);
+        if constexpr ((TM & 1) != 0) b2.prologue(c, hdr, 0, dealt);
+        if constexpr (!residual_late) rs.prologue(c, hdr, dealt);
+    };
     ECS_STAMP(c, 1);            // panel header here
-    if constexpr ((TM & 8) != 0) b16.prologue(c, hdr, 3, dealt);
-    if constexpr ((TM & 4) != 0) b8.prologue(c, hdr, 2, dealt);
-    if constexpr ((TM & 2) != 0) b4.prologue(c, hdr, 1, dealt);
-    if constexpr ((TM & 1) != 0) b2.prologue(c, hdr, 0, dealt);
-    if constexpr (!residual_late) rs.prologue(c, hdr, dealt);
+    if constexpr (NB == 1) request_first();
     ECS_STAMP(c, 2);            // first chunks of every set requested
 
 #ifdef ECS_TRACE
@@ -853,7 +862,8 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     auto put = [&](uint32_t idx, const uint4 &t) { *(idx < nmeta ? meta4 + idx : lds4 + (idx - nmeta)) = t; };
     put(piece_index(0), s0);
     if constexpr (K > 1) put(piece_index(1), s1);
-    if constexpr (K > 2) put(piece_index(2), s2), put(piece_index(3), s3);
+    if constexpr (K > 2) put(piece_index(2), s2);
+    if constexpr (K > 3) put(piece_index(3), s3);
     static_assert(K <= 4, "at most four pieces per thread are brought here");
     // With K < 4 the list is covered (the launch counts its pieces); what is left with K = 4 comes in rounds of U loads per
     // thread that travel together (a round is a trip to the L2 or beyond).  One vector: two, as far as the registers of the
@@ -900,6 +910,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     } else {
         for (uint32_t i = (x_fast ? nvec * 8u : 0u) + tid; i < n; i += nt) xs[i] = x[i];
     }
+    if constexpr (NB > 1) request_first();
     ECS_STAMP(c, 3);            // this wavefront's pieces of the tables and x written to LDS
     __syncthreads();
     ECS_STAMP(c, 4);            // first barrier passed
@@ -1206,7 +1217,7 @@ template <int TM, int DB, bool BATCH, int K, int NB, int VW = 2>
 static int launch_k(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, void *stream)
 {
     if constexpr (BATCH) return launch_m<TM, DB, 2, K, NB, VW>(batch, threads, lds_bytes, stream);
-    if constexpr (NB > 2)                     // (two right-hand sides are refused where they do not fit in one phase)
+    if constexpr (NB > 2 && K == 4)           // (two right-hand sides are refused where they do not fit in one phase)
         if (batch.per_phase) return launch_m<TM, DB, 3, K, NB, VW>(batch, threads, lds_bytes, stream);
     if (batch.count == 1) return launch_m<TM, DB, 0, K, NB, VW>(batch, threads, lds_bytes, stream);
     if constexpr (NB == 1) return launch_m<TM, DB, 1, K, NB, VW>(batch, threads, lds_bytes, stream);
@@ -1256,14 +1267,33 @@ static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes
                            : launch_b<TM, 8, false>(batch, threads, lds_bytes, stream);
 }
 
-// several right-hand sides: one matrix per launch, the widest staging variant, images with 8-grained sets at most
+// several right-hand sides: one matrix per launch, images with 8-grained sets at most; the staging variant as with one vector
+// (us, two, 5120 x 5120 at 30 %, two pieces per thread: by the variant for four 6.38, for two 5.85;
+// four, 16384 x 1024 at 30 %, one piece 5.55 / 4.80, 5120 x 5120 at 30 %, 8-bit, three 7.35 / 6.90; six or eight
+// at once are slower than four and a loop: FP32 4096 x 4096, four, 6.81 / 7.55 / 7.48).  Phases are for an X that takes them all.
+template <int TM, int DB, int NB, int VW>
+static int launch_nk(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, void *stream)
+{
+    const EcsBatchItem &it = batch.item[0];
+    const bool pieces_of_x = (reinterpret_cast<uintptr_t>(it.x) & 15) == 0 && it.row_stride == NB;       // else x comes value by value
+    const uint32_t pieces = it.meta_stride / 16u + (pieces_of_x ? it.n * NB * VW / 16u : 0u);
+    const uint32_t per_thread = batch.per_phase ? 4u : (pieces + threads - 1u) / threads;
+    switch (per_thread) {
+    case 0:
+    case 1: return launch_k<TM, DB, false, 1, NB, VW>(batch, threads, lds_bytes, stream);
+    case 2: return launch_k<TM, DB, false, 2, NB, VW>(batch, threads, lds_bytes, stream);
+    case 3: return launch_k<TM, DB, false, 3, NB, VW>(batch, threads, lds_bytes, stream);
+    default: return launch_k<TM, DB, false, 4, NB, VW>(batch, threads, lds_bytes, stream);
+    }
+}
+
 template <int TM, int DB, int VW = 2>
 static int launch_nb(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, uint32_t nb, void *stream)
 {
     switch (nb) {
-    case 2: return launch_k<TM, DB, false, 4, 2, VW>(batch, threads, lds_bytes, stream);
-    case 4: return launch_k<TM, DB, false, 4, 4, VW>(batch, threads, lds_bytes, stream);
-    case 8: return launch_k<TM, DB, false, 4, 8, VW>(batch, threads, lds_bytes, stream);
+    case 2: return launch_nk<TM, DB, 2, VW>(batch, threads, lds_bytes, stream);
+    case 4: return launch_nk<TM, DB, 4, VW>(batch, threads, lds_bytes, stream);
+    case 8: return launch_nk<TM, DB, 8, VW>(batch, threads, lds_bytes, stream);
     default: return (int)hipErrorInvalidValue;
     }
 }
