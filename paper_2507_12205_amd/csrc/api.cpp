@@ -405,7 +405,7 @@ int ecspmv_run_batch(const ecspmv_matrix *const *As, const void *const *d_xs, vo
             const int t = As[base + i]->image.threads_per_wg;
             if (t) threads = (uint32_t)t;                      // a build-time choice overrides
         }
-        int s = hip_status(ecs::launch_ecspmv(b, threads, lds, mask, (uint32_t)bits, (uint32_t)vbits, stream));
+        int s = hip_status(ecs::launch_ecspmv(b, threads, lds, mask, (uint32_t)bits, (uint32_t)vbits, chunks, stream));
         if (s) return s;
     }
     return ECSPMV_OK;

@@ -1257,7 +1257,7 @@ static int launch_b(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
 
 template <int TM>
 static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, uint32_t delta_bits, uint32_t value_bits,
-                     void *stream)
+                     uint64_t chunks, void *stream)
 {
     // FP32 values: lone-launch buffer depths
     if (value_bits == 32) {
@@ -1267,13 +1267,18 @@ static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes
     }
     // index compression switched off (absolute 16-bit columns): the ablation point, one variant per set mask
     if (delta_bits == 16) return launch_k<TM, 16, false, 4, 1>(batch, threads, lds_bytes, stream);
-    // Residual-only images and images with one block set have a second variant for launches that carry several
-    // SpMVs.  The residual-only one (deeper buffers) was measured at 2, 3 and 7 512-thread workgroups per compute unit: slower,
-    // 1 % slower, faster.  Around the line of 768 workgroups it gains little or loses, us with shallow / deep buffers: 256
-    // threads 12 x 1024 x 1024 at 30 % (768) 4.30 / 4.28, 13 of them (832) 4.59 / 4.50, 12 x 1408 x 597 at 20 % (1056) 4.01 / 4.31;
-    // 512 threads 3 x 4096 x 4096 at 20 % (768) 6.49 / 6.77, four (1024) 7.85 / 8.40, 4 x 5120 x 5120 at 30 % (1024) 14.05 / 14.22.
-    const uint32_t grid = batch.item[batch.count - 1].block_end;
-    if ((TM == 0 && batch.count > 1 && grid > 768) || (TM == 1 && batch.count > 1))
+    // Residual-only images and images with one block set have a second variant for launches that carry several SpMVs.  The
+    // residual-only one (two buffers) keeps more on the way, which pays where a wavefront has many chunks to go through and
+    // the launch is more than one round: us with one / two buffers, 3 x 11008 x 4096 at 30 % (52 chunks a panel) 18.30 / 17.87, 4 x
+    // 5120 x 13824 (79) 35.8 / 33.3, 4 x 8192 x 8192, 8-bit (77) 38.0 / 37.1; but 3 x 8192 x 4096 (39) 13.55 / 14.43, 8 x 2048 x 2048 at 20 % (7)
+    // 5.5 / 6.2, 8 x 4096 x 4096 at 30 %, 8-bit (19) 20.6 / 21.8, and 2 x 13824 x 5120 (80, 512 workgroups) 18.66 / 18.93.
+    // The one-block-set one requests every set before the first barrier, which pays where a wavefront has little more than that:
+    // us with the residual set after the barrier / before it, 3 x 768 x 768 at 30 %, 8-bit (5) 3.39 / 3.29, 4 x 512 x 512 at 50 % (5) 3.37 / 3.27, 8 x
+    // 2048 x 512 (5) 4.94 / 4.86; 16 x 768 x 768 (8) 4.86 / 4.85; but 16 x 1408 x 1408 at 30 %, 8-bit (9.4) 6.66 / 6.78, at 50 % (15) 8.92 / 9.14, 8 x 600 x
+    // 1700 (18) 4.96 / 5.17, 2 x 4096 x 4096 (43) 8.97 / 9.39.
+    const uint64_t grid = batch.item[batch.count - 1].block_end;
+    const bool second = TM == 0 ? grid > 512u && chunks > 45u * grid : TM == 1 && chunks <= 9u * grid;
+    if (batch.count > 1 && second)
         return delta_bits == 4 ? launch_b<TM, 4, TM <= 1>(batch, threads, lds_bytes, stream)
                                : launch_b<TM, 8, TM <= 1>(batch, threads, lds_bytes, stream);
     return delta_bits == 4 ? launch_b<TM, 4, false>(batch, threads, lds_bytes, stream)
@@ -1341,16 +1346,16 @@ int launch_ecspmv_multi(const EcsBatch &batch, uint32_t threads, uint32_t lds_by
 }
 
 int launch_ecspmv(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, uint32_t type_mask, uint32_t delta_bits,
-                  uint32_t value_bits, void *stream)
+                  uint32_t value_bits, uint64_t chunks, void *stream)
 {
     // one instantiation per highest granularity present: sets that do not occur cost no registers
     const int top = (type_mask & 8) ? 15 : (type_mask & 4) ? 7 : (type_mask & 2) ? 3 : (type_mask & 1) ? 1 : 0;
     switch (top) {
-    case 15: return launch_tm<15>(batch, threads, lds_bytes, delta_bits, value_bits, stream);
-    case 7: return launch_tm<7>(batch, threads, lds_bytes, delta_bits, value_bits, stream);
-    case 3: return launch_tm<3>(batch, threads, lds_bytes, delta_bits, value_bits, stream);
-    case 1: return launch_tm<1>(batch, threads, lds_bytes, delta_bits, value_bits, stream);
-    default: return launch_tm<0>(batch, threads, lds_bytes, delta_bits, value_bits, stream);
+    case 15: return launch_tm<15>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, stream);
+    case 7: return launch_tm<7>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, stream);
+    case 3: return launch_tm<3>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, stream);
+    case 1: return launch_tm<1>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, stream);
+    default: return launch_tm<0>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, stream);
     }
 }
 
