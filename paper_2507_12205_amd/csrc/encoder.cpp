@@ -189,14 +189,29 @@ inline uint64_t stored_bits(const uint32_t *v, int count)
     return out;
 }
 
-// The rows as the encoder reads them: nw words of bits each, and how many are set.  With a CSR matrix behind it, `rank` holds
-// how many entries of a row lie before each word.
+// The rows as the encoder reads them: nw words of bits each, and how many are set.  The bits of a dense matrix are made once (a
+// sixteenth of its size at most), and so are those of a CSR matrix where they take no more than its entries do (8 bytes each).
+// Otherwise, tall and very sparse, they are made of one panel at a time, whenever they are read: 1 000 000 x 60 000 with two
+// entries per row would be 7.5 GB of bits beside 16 MB of entries.
 struct Rows {
     int nw = 0;
-    RawVector<uint64_t> bits;
-    RawVector<uint32_t> rank;
+    const Csr *csr = nullptr;
+    RawVector<uint64_t> bits;             // empty: made when they are read
     std::vector<int64_t> count;
     const uint64_t *row(int64_t i) const { return bits.data() + (size_t)i * nw; }
+    void from_csr(int64_t i, uint64_t *to) const
+    {
+        std::memset(to, 0, 8 * (size_t)nw);
+        for (int64_t p = csr->rowptr[(size_t)i]; p < csr->rowptr[(size_t)i + 1]; ++p) {
+            const int32_t c = csr->col[(size_t)p];
+            to[c >> 6] |= 1ull << (c & 63);
+        }
+    }
+    void read(int64_t i, uint64_t *to) const
+    {
+        if (bits.empty()) from_csr(i, to);
+        else std::memcpy(to, row(i), 8 * (size_t)nw);
+    }
 };
 
 template <typename T>
@@ -222,55 +237,17 @@ void read_dense(const Source &A, int threads, Rows &out)
 void read_rows(const Source &A, int threads, Rows &out)
 {
     out.nw = (int)((A.n + 63) / 64);
-    out.bits.resize((size_t)A.m * out.nw);
+    out.csr = A.csr;
     out.count.resize((size_t)A.m);
-    if (!A.csr) {
-        if (A.value_bits == 16) read_dense<uint16_t>(A, threads, out);
-        else read_dense<uint32_t>(A, threads, out);
-        return;
+    if (A.csr) {
+        for (int64_t i = 0; i < A.m; ++i) out.count[(size_t)i] = A.csr->rowptr[(size_t)i + 1] - A.csr->rowptr[(size_t)i];
+        if (A.m * out.nw > A.csr->rowptr[(size_t)A.m]) return;
     }
-    out.rank.resize((size_t)A.m * out.nw);
-    parallel_for(A.m, threads, [&](int64_t i) {
-        uint64_t *b = out.bits.data() + (size_t)i * out.nw;
-        std::memset(b, 0, 8 * (size_t)out.nw);
-        for (int64_t p = A.csr->rowptr[(size_t)i]; p < A.csr->rowptr[(size_t)i + 1]; ++p) {
-            const int32_t c = A.csr->col[(size_t)p];
-            b[c >> 6] |= 1ull << (c & 63);
-        }
-        uint32_t before = 0;
-        for (int w = 0; w < out.nw; ++w) {
-            out.rank[(size_t)i * out.nw + w] = before;
-            before += (uint32_t)__builtin_popcountll(b[w]);
-        }
-        out.count[(size_t)i] = before;
-    });
+    out.bits.resize((size_t)A.m * out.nw);
+    if (A.csr) parallel_for(A.m, threads, [&](int64_t i) { out.from_csr(i, out.bits.data() + (size_t)i * out.nw); });
+    else if (A.value_bits == 16) read_dense<uint16_t>(A, threads, out);
+    else read_dense<uint32_t>(A, threads, out);
 }
-
-// value of a stored entry
-template <typename T>
-struct DenseValues {
-    const T *W;
-    int64_t ld;
-    struct Row {
-        const T *v;
-        uint32_t operator[](uint32_t col) const { return v[col]; }
-    };
-    Row row(int64_t i) const { return {W + i * ld}; }
-};
-struct CsrValues {
-    const Csr *A;
-    const Rows *rows;
-    struct Row {
-        const uint32_t *v, *rank;
-        const uint64_t *bits;
-        uint32_t operator[](uint32_t col) const
-        {
-            const uint32_t w = col >> 6;
-            return v[rank[w] + (uint32_t)__builtin_popcountll(bits[w] & ((1ull << (col & 63)) - 1ull))];
-        }
-    };
-    Row row(int64_t i) const { return {A->val.data() + A->rowptr[(size_t)i], rows->rank.data() + (size_t)i * rows->nw, rows->row(i)}; }
-};
 
 // ------------------------------------------------------------------------------------------------------
 // hierarchical block extraction inside one panel
@@ -297,7 +274,7 @@ struct PanelUnits {
         std::vector<uint16_t> cols;
         uint32_t size() const { return (uint32_t)block_len.size(); }
     } units[ECS_NUM_BTYPES];
-    std::vector<uint64_t> resid;          // bits of the residual entries, row by row
+    std::vector<uint64_t> resid;          // bits of the residual entries, row by row (empty where they are found again when the panel is written)
 };
 
 inline int popcount_and(const uint64_t *a, const uint64_t *b, int nw)
@@ -419,7 +396,7 @@ void extract_panel(const Rows &A, const int32_t *prow, int nrows, int max_g, int
         L.nw = nw, L.width = 1;
         L.bits.resize((size_t)nrows * nw);
         for (int r = 0; r < nrows; ++r) {
-            std::memcpy(L.row(r), A.row(prow[r]), 8 * (size_t)nw);
+            A.read(prow[r], L.row(r));
             L.members.push_back(r);
             L.cnt.push_back((int)A.count[(size_t)prow[r]]);
         }
@@ -636,9 +613,138 @@ void lay_out_panel(const Rows &A, const int32_t *prow, int nrows, const PanelUni
     hdr[PH_PANEL_BYTES] = (uint32_t)out.bytes;
 }
 
+// f(column, value) for every set bit of a row in turn
+template <class Row, class F>
+inline void for_each_entry(const uint64_t *bits, int nw, const Row &row, F &&f)
+{
+    for (int w = 0; w < nw; ++w)
+        for (uint64_t m = bits[w]; m; m &= m - 1) {
+            const int32_t col = 64 * w + __builtin_ctzll(m);
+            f(col, row[(uint32_t)col]);
+        }
+}
+
+// Where the values of a panel's stored entries come from: row(r)[column], and the residual entries of row r in turn, as
+// f(column, value).
+template <typename T>
+struct DensePanel {
+    const T *W;
+    int64_t ld;
+    const int32_t *prow;
+    const uint64_t *resid;
+    int nw;
+    struct Row {
+        const T *v;
+        uint32_t operator[](uint32_t col) const { return v[col]; }
+    };
+    Row row(int r) const { return {W + (int64_t)prow[r] * ld}; }
+    void blocks_written() {}
+    template <class F>
+    void residual(int r, F &&f) const
+    {
+        for_each_entry(resid + (size_t)r * nw, nw, row(r), f);
+    }
+};
+
+// An entry's place in its row is how many bits are set before its column: `rank` holds how many before each word (a row has fewer
+// than 65536 columns).
+struct CsrRow {
+    const uint32_t *v;
+    const uint16_t *rank;
+    const uint64_t *bits;
+    uint32_t operator[](uint32_t col) const
+    {
+        const uint32_t w = col >> 6;
+        return v[rank[w] + (uint32_t)__builtin_popcountll(bits[w] & ((1ull << (col & 63)) - 1ull))];
+    }
+};
+inline void rank_words(const uint64_t *bits, int nw, uint16_t *rank)
+{
+    uint32_t before = 0;
+    for (int w = 0; w < nw; ++w) {
+        rank[w] = (uint16_t)before;
+        before += (uint32_t)__builtin_popcountll(bits[w]);
+    }
+}
+
+// a CSR matrix whose bits were kept
+struct CsrPanel {
+    const Rows &rows;
+    const int32_t *prow;
+    const uint64_t *resid;
+    std::vector<uint16_t> rank;
+    CsrPanel(const Rows &all, const int32_t *panel_rows, int nrows, const PanelUnits &pu)
+        : rows(all), prow(panel_rows), resid(pu.resid.data()), rank((size_t)nrows * all.nw)
+    {
+        for (int r = 0; r < nrows; ++r) rank_words(rows.row(prow[r]), rows.nw, rank.data() + (size_t)r * rows.nw);
+    }
+    CsrRow row(int r) const
+    {
+        return {rows.csr->val.data() + rows.csr->rowptr[(size_t)prow[r]], rank.data() + (size_t)r * rows.nw, rows.row(prow[r])};
+    }
+    void blocks_written() {}
+    template <class F>
+    void residual(int r, F &&f) const
+    {
+        for_each_entry(resid + (size_t)r * rows.nw, rows.nw, row(r), f);
+    }
+};
+
+// A CSR matrix whose bits were not: a panel with units makes its own, and takes the units' columns out of them once the blocks are
+// written.  Without units every entry is a residual one.
+struct SparseCsrPanel {
+    const Rows &rows;
+    const int32_t *prow;
+    const PanelUnits &pu;
+    std::vector<uint64_t> bits;
+    std::vector<uint16_t> rank;
+    SparseCsrPanel(const Rows &all, const int32_t *panel_rows, int nrows, const PanelUnits &units)
+        : rows(all), prow(panel_rows), pu(units)
+    {
+        bool any = false;
+        for (auto &set : pu.units) any |= set.size() != 0;
+        if (!any) return;
+        bits.resize((size_t)nrows * rows.nw);
+        rank.resize((size_t)nrows * rows.nw);
+        for (int r = 0; r < nrows; ++r) {
+            rows.read(prow[r], bits.data() + (size_t)r * rows.nw);
+            rank_words(bits.data() + (size_t)r * rows.nw, rows.nw, rank.data() + (size_t)r * rows.nw);
+        }
+    }
+    CsrRow row(int r) const
+    {
+        return {rows.csr->val.data() + rows.csr->rowptr[(size_t)prow[r]], rank.data() + (size_t)r * rows.nw, bits.data() + (size_t)r * rows.nw};
+    }
+    void blocks_written()
+    {
+        for (int t = 0; t < ECS_NUM_BTYPES; ++t) {
+            const PanelUnits::Set &set = pu.units[t];
+            const uint32_t g = 2u << t;
+            for (uint32_t u = 0; u < set.size(); ++u)
+                for (uint32_t r = 0; r < g; ++r) {
+                    uint64_t *b = bits.data() + (size_t)set.rows[(size_t)g * u + r] * rows.nw;
+                    for (uint32_t k = 0; k < ECS_UNIT_COLS; ++k) {
+                        const uint32_t col = set.cols[(size_t)ECS_UNIT_COLS * u + k];
+                        b[col >> 6] &= ~(1ull << (col & 63));
+                    }
+                }
+        }
+    }
+    template <class F>
+    void residual(int r, F &&f) const
+    {
+        const Csr &A = *rows.csr;
+        const uint64_t *b = bits.empty() ? nullptr : bits.data() + (size_t)r * rows.nw;
+        for (int64_t p = A.rowptr[(size_t)prow[r]]; p < A.rowptr[(size_t)prow[r] + 1]; ++p) {
+            const int32_t col = A.col[(size_t)p];
+            if (!b || (b[col >> 6] >> (col & 63) & 1)) f(col, A.val[(size_t)p]);
+        }
+    }
+};
+
 // Writes a panel to P, which holds zeros.
 template <typename T, class Values>
-void encode_panel(const Values &values, const int32_t *prow, int nrows, int nw, const PanelUnits &pu, bool reorder, int delta_bits,
+void encode_panel(Values &&values, const int32_t *prow, int nrows, const PanelUnits &pu, bool reorder, int delta_bits,
                   PanelLayout &lay, uint8_t *P)
 {
     const uint32_t *hdr = lay.hdr;
@@ -683,7 +789,7 @@ void encode_panel(const Values &values, const int32_t *prow, int nrows, int nw, 
             T *v = (T *)(P + hdr[PH_BV_OFF + t] + 64ull * vw * g * u);
             for (uint32_t r = 0; r < g; ++r) {
                 ue[1 + r] = (uint16_t)cursor[rows[r]]++;
-                const auto row = values.row(prow[rows[r]]);
+                const auto row = values.row(rows[r]);
                 const uint32_t *to = place.data() + r * ECS_UNIT_COLS;
                 for (unsigned k = 0; k < ECS_UNIT_COLS; ++k) v[to[k]] = (T)row[cols[k]];
             }
@@ -698,10 +804,9 @@ void encode_panel(const Values &values, const int32_t *prow, int nrows, int nw, 
     EcsREntry *rentries = (EcsREntry *)(P + hdr[PH_RENTRY_OFF]);
     uint32_t lane = 0, nentries = 0;
     int64_t scan = 0;                                     // sum of the deltas of earlier lanes in this chunk
+    values.blocks_written();
     for (int r = 0; r < nrows; ++r) {
         if (lay.rowlu[(size_t)r] == lay.rowlu[(size_t)r + 1]) continue;
-        const uint64_t *bits = pu.resid.data() + (size_t)r * nw;
-        const auto row = values.row(prow[r]);
         uint8_t *d = nullptr;
         T *v = nullptr;
         uint32_t e = 0, stride = 0;                       // element of the lane unit; values from one load of a lane to the next
@@ -738,23 +843,21 @@ void encode_panel(const Values &values, const int32_t *prow, int nrows, int nw, 
             scan += delta;
             if (++e == ECS_LANE_ELEMS) e = 0, ++lane;
         };
-        for (int w = 0; w < nw; ++w)
-            for (uint64_t m = bits[w]; m; m &= m - 1) {
-                const int32_t col = 64 * w + __builtin_ctzll(m);
-                if (cur < 0) {
-                    put(0, row[(uint32_t)col], col);
-                } else {
-                    int32_t gap = col - cur;
-                    while (gap > max_delta) {             // explicit zero every R_P - 1 columns (Section 6.2)
-                        put((uint32_t)max_delta, 0, cur);
-                        cur += max_delta;
-                        gap -= max_delta;
-                    }
-                    put((uint32_t)gap, row[(uint32_t)col], cur);
-                    ++lay.delta_hist[hist_bin((unsigned)gap)];
+        values.residual(r, [&](int32_t col, uint32_t value) {
+            if (cur < 0) {
+                put(0, value, col);
+            } else {
+                int32_t gap = col - cur;
+                while (gap > max_delta) {                 // explicit zero every R_P - 1 columns (Section 6.2)
+                    put((uint32_t)max_delta, 0, cur);
+                    cur += max_delta;
+                    gap -= max_delta;
                 }
-                cur = col;
+                put((uint32_t)gap, value, cur);
+                ++lay.delta_hist[hist_bin((unsigned)gap)];
             }
+            cur = col;
+        });
         while (e) put(0, 0, cur);                         // tail alignment: zero-valued elements on the last column
     }
     if (lane != nlanes || nentries != hdr[PH_NRENTRIES]) lay.err = -100;
@@ -784,7 +887,8 @@ static void cluster_rows(const Rows &A, int group, int threads, std::vector<int3
     std::vector<Grp> cur((size_t)m);
     parallel_for(m, threads, [&](int64_t i) {
         Grp &g = cur[(size_t)i];
-        g.bits.assign(A.row(i), A.row(i) + nw);
+        g.bits.resize(nw);
+        A.read(i, g.bits.data());
         g.cnt = (int)A.count[(size_t)i];
         g.members.assign(1, (int32_t)i);
     });
@@ -926,6 +1030,7 @@ int build_image(const Source &A, const BuildParams &bp, Image &out)
             const int nrows = (int)(bound[p + 1] - bound[p]);
             extract_panel(rows, prow, nrows, max_g, bp.max_rounds, bp.delta_bits, units[p]);
             lay_out_panel(rows, prow, nrows, units[p], bp.delta_bits, A.value_bits, lays[p]);
+            if (rows.bits.empty()) std::vector<uint64_t>().swap(units[p].resid);
         });
         if (bp.keep_small_sets || max_g == 1) break;
         int top = 0;                                                         // coarsest set present
@@ -956,20 +1061,22 @@ int build_image(const Source &A, const BuildParams &bp, Image &out)
     const uint64_t total = ECS_IMAGE_HEADER + (uint64_t)stride * (uint64_t)P + 4096u;
     if (total > 0xFFFFFFFF00ull) return -2;
     out.bytes.resize((size_t)total);                                         // not filled: every byte is written below
-    auto encode = [&](auto values, auto zero) {
+    auto encode = [&](auto zero) {
         typedef decltype(zero) T;
         parallel_for(P, threads, [&](int64_t p) {
             uint8_t *to = out.bytes.data() + ECS_IMAGE_HEADER + (size_t)stride * (size_t)p;
             std::memset(to, 0, stride + (p + 1 == P ? 4096u : 0u));
-            encode_panel<T>(values, order.data() + bound[p], (int)(bound[p + 1] - bound[p]), rows.nw, units[p], bp.reorder,
-                            bp.delta_bits, lays[p], to);
+            const int32_t *prow = order.data() + bound[p];
+            const int nrows = (int)(bound[p + 1] - bound[p]);
+            auto from = [&](auto &&values) { encode_panel<T>(values, prow, nrows, units[p], bp.reorder, bp.delta_bits, lays[p], to); };
+            if (!A.csr) from(DensePanel<T>{static_cast<const T *>(A.dense), A.ld, prow, units[p].resid.data(), rows.nw});
+            else if (rows.bits.empty()) from(SparseCsrPanel(rows, prow, nrows, units[p]));
+            else from(CsrPanel(rows, prow, nrows, units[p]));
             units[p] = PanelUnits();
         });
     };
-    if (A.csr && A.value_bits == 16) encode(CsrValues{A.csr, &rows}, uint16_t(0));
-    else if (A.csr) encode(CsrValues{A.csr, &rows}, uint32_t(0));
-    else if (A.value_bits == 16) encode(DenseValues<uint16_t>{static_cast<const uint16_t *>(A.dense), A.ld}, uint16_t(0));
-    else encode(DenseValues<uint32_t>{static_cast<const uint32_t *>(A.dense), A.ld}, uint32_t(0));
+    if (A.value_bits == 16) encode(uint16_t(0));
+    else encode(uint32_t(0));
     for (auto &lay : lays)
         if (lay.err) return lay.err;
     out.m = m;

@@ -1,5 +1,9 @@
-"""The two ways into the encoder (dense rows and CSR) give the same image, and block columns are cut into units as defined where
-runs end inside a word of 64 columns, at its edge, or at the largest delta."""
+"""The two ways into the encoder (dense rows and CSR) give the same image, a CSR matrix takes memory by its entries, and block
+columns are cut into units as defined where runs end inside a word of 64 columns, at its edge, or at the largest delta."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import scipy.sparse as sp
@@ -41,6 +45,66 @@ def test_dense_and_csr_builds_agree(m, n, ld, dtype, delta_bits):
     back = np.zeros((m, n), dtype=dtype)
     back[r, c] = v.view(dtype)
     assert np.array_equal(back, W) and r.size == np.count_nonzero(W)
+
+
+def _both(W, opts):
+    """the images of W built from its rows and from CSR"""
+    S = sp.csr_matrix(W.astype(np.float64))
+    S.sort_indices()
+    f32 = W.dtype == np.float32
+    a = (E.ecspmv_build_dense_f32 if f32 else E.ecspmv_build_dense)(W, opts)
+    b = (E.ecspmv_build_csr_f32 if f32 else E.ecspmv_build_csr)(S.indptr, S.indices, S.data.astype(W.dtype), *W.shape, opts)
+    return a, b
+
+
+# the bits of a CSR matrix are kept where a row has an entry per word of 64 columns or more, else made panel by panel, and not at all
+# in panels without units
+@pytest.mark.parametrize("flags", [0, binding.FLAG_CLUSTER_ROWS, binding.FLAG_GLOBAL_MATCHING])
+@pytest.mark.parametrize("background,blocks,kept", [(0, 0, False), (1, 0, False), (1, 1, False), (33, 0, False), (34, 0, True),
+                                                    (14, 1, False), (20, 1, True), (60, 2, True)])
+@pytest.mark.parametrize("dtype,delta_bits", [(np.float16, 4), (np.float16, 8), (np.float16, 16), (np.float32, 8)])
+def test_sparse_csr_builds_agree(background, blocks, kept, flags, dtype, delta_bits):
+    m, n, words = 60, 2150, 34                            # 34 words of 64 columns, the last one not full
+    rng = np.random.default_rng(100 * background + blocks)
+    W = np.zeros((m, n), dtype=dtype)
+    for i in range(m):
+        W[i, rng.choice(n, background, replace=False)] = rng.standard_normal(background)
+    for k in range(blocks):                               # rows of one panel and of several
+        rows = np.arange(8) + 16 * k if k % 2 == 0 else rng.choice(m, 8, replace=False)
+        W[np.ix_(rows, 200 * k + np.arange(130))] = 1.0 + k
+    dense, csr = _both(W, E.make_opts(delta_bits=delta_bits, num_panels=4, flags=flags))
+    assert np.array_equal(dense.ecspmv_export_image(), csr.ecspmv_export_image())
+    assert (sum(csr.ecspmv_stats().units_by_g[1:]) > 0) == (blocks > 0)
+    assert (np.count_nonzero(W) >= m * words) == kept
+
+
+CHILD = r"""
+import sys
+sys.modules["torch"] = None                               # the library alone
+sys.path.insert(0, sys.argv[1])
+import numpy as np
+from paper_2507_12205_amd import binding as B
+m, n = 400000, 10000
+first = np.random.default_rng(1).integers(0, n - 1, m)
+col = np.stack([first, first + 1], 1).astype(np.int32).ravel()
+args = np.arange(m + 1, dtype=np.int64) * 2, col, np.ones(2 * m, np.float16), m, n, B.make_opts(num_threads=2)
+peak = lambda: int(open("/proc/self/status").read().split("VmHWM:")[1].split()[0]) * 1024
+before = peak()
+A = B.ecspmv_build_csr(*args)
+print(peak() - before, A.ecspmv_device_bytes())
+"""
+
+
+def test_memory_of_a_tall_sparse_csr_build():
+    """Beyond the image: a copy of the entries (8 bytes each), and per row a few tables of 4 or 8 bytes and its share of the panels in
+    work.  A bit for every column of every row would be 500 MB."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", CHILD, root], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-2000:]
+    grown, image = map(int, res.stdout.split())
+    m, n, panels, threads = 400000, 10000, 256, 2
+    in_work = threads * (m // panels + 1) * (n // 64 + 1) * 8 * 2          # bits of a panel, and as much again on top
+    assert grown < image + 8 * 2 * m + 100 * m + in_work + (32 << 20), (grown, image)
 
 
 def _units(cols, max_delta):
