@@ -3,6 +3,7 @@
 #include <atomic>
 #include <cstddef>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -151,18 +152,12 @@ int parse_opts(const ecspmv_build_opts *o, ecs::BuildParams &bp, int value_bits 
 
 int finish_build(const ecs::Source &A, const ecs::BuildParams &bp, ecspmv_matrix **out)
 {
-    ecspmv_matrix *h = new (std::nothrow) ecspmv_matrix;
+    std::unique_ptr<ecspmv_matrix> h(new (std::nothrow) ecspmv_matrix);       // released on every way out but the last
     if (!h) return ECSPMV_ERR_NOMEM;
-    int e = ecs::build_image(A, bp, h->image);
-    if (e) {
-        delete h;
-        return map_build_error(e);
-    }
-    if (h->image.lds_bytes > 160u * 1024u) {
-        delete h;
-        return ECSPMV_ERR_UNSUPPORTED;
-    }
-    *out = h;
+    const int e = ecs::build_image(A, bp, h->image);
+    if (e) return map_build_error(e);
+    if (h->image.lds_bytes > 160u * 1024u) return ECSPMV_ERR_UNSUPPORTED;
+    *out = h.release();
     return ECSPMV_OK;
 }
 
@@ -487,7 +482,7 @@ int ecspmv_csr_build_dense(const uint16_t *W, int64_t m, int64_t n, int64_t ld, 
         ecs::Csr A;
         ecs::csr_from_dense(W, m, n, ld, 0, A);
         if (A.rowptr[(size_t)m] > 0x7fffffff || m > 0x7ffffffe) return ECSPMV_ERR_UNSUPPORTED;
-        ecspmv_csr *c = new (std::nothrow) ecspmv_csr;
+        std::unique_ptr<ecspmv_csr> c(new (std::nothrow) ecspmv_csr);
         if (!c) return ECSPMV_ERR_NOMEM;
         c->m = m;
         c->n = n;
@@ -500,7 +495,7 @@ int ecspmv_csr_build_dense(const uint16_t *W, int64_t m, int64_t n, int64_t ld, 
         c->off_col = up(4 * ((size_t)m + 1));
         c->off_val = c->off_col + up(4 * (size_t)c->nnz);
         c->bytes = c->off_val + up(2 * (size_t)c->nnz) + 256;
-        *out = c;
+        *out = c.release();
         return ECSPMV_OK;
     } catch (const std::bad_alloc &) {
         return ECSPMV_ERR_NOMEM;

@@ -133,3 +133,34 @@ def test_runs_are_cut_where_the_gap_exceeds_the_largest_delta(delta_bits, gaps, 
         g, _, unit_cols = A.ecspmv_block_sets()
         want = _units(cols, 2 ** delta_bits - 1)
         assert len(g) == len(want) and np.array_equal(unit_cols.reshape(-1, 64), np.array(want).reshape(-1, 64))
+
+
+LEAK = r"""
+import ctypes, resource, sys
+sys.modules["torch"] = None
+sys.path.insert(0, sys.argv[1])
+import numpy as np
+from paper_2507_12205_amd import binding as B
+class Info(ctypes.Structure):
+    _fields_ = [(k, ctypes.c_size_t) for k in ("arena", "ordblks", "smblks", "hblks", "hblkhd", "usmblks", "fsmblks", "uordblks", "fordblks",
+                                               "keepcost")]
+info = ctypes.CDLL(None).mallinfo2
+info.restype = Info
+lib, W, out = B.lib(), np.zeros((60000, 20000), np.uint16), ctypes.c_void_p(0)     # 150 MB of bits
+build = lambda: lib.ecspmv_build_dense(W.ctypes.data, *W.shape, W.shape[1], None, ctypes.byref(out))
+size = int(open("/proc/self/status").read().split("VmSize:")[1].split()[0]) * 1024
+resource.setrlimit(resource.RLIMIT_AS, (size + (64 << 20), -1))
+statuses = {build()}
+before = info().uordblks
+for _ in range(1000):
+    statuses.add(build())
+print(sorted(statuses) == [B.ERR_NOMEM], info().uordblks - before)
+"""
+
+
+def test_a_build_that_runs_out_of_memory_leaves_nothing_behind():
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", LEAK, root], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-2000:]
+    refused, left = res.stdout.split()
+    assert refused == "True" and int(left) < 100 * 1000         # less than a hundred bytes a call
