@@ -820,16 +820,12 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     if constexpr (K > 2) s2 = *piece(2);
     if constexpr (K > 3) s3 = *piece(3);
     ECS_STAMP(c, 20);           // header and first pieces requested
-    // What whole pieces leave of an aligned x, up to seven values: the first wavefront brings them right behind its pieces.  (After
-    // the requests for the first chunks they came behind those, a trip to HBM before the barrier, and with that loop in the way the
-    // barrier waited for more than it had to in every launch.  us after / before: eight 608 x 1700 at 50 % 5.35 -> 4.96, twelve 1024 x 1500
-    // 6.87 -> 6.22, 2999 x 5003 at 30 % 4.71 -> 4.57, with 8-bit deltas 4.93 -> 4.86; and no tail at all, 5120 x 5120 at 30 % from the
-    // Infinity Cache 5.69 -> 5.29.)
-    const uint32_t tail0 = nvec * 8u;
-    if (x_fast && tail0 != n && c.wave == 0u) {
-        const uint32_t i = tail0 + c.lane;
-        if (i < n) xs[i] = x[i];
-    }
+    // What whole pieces leave of an aligned x, up to seven values: one thread for each brings them right behind its pieces.  (After
+    // the requests for the first chunks they came behind those, a trip to HBM before the barrier: us there / here, eight 608 x 1700 at
+    // 50 % 5.07 / 4.95, twelve 1024 x 1500 at 30 % 5.07 / 4.85, five 1001 x 2047 at 40 %, 8-bit 5.27 / 4.9, six 601 x 1701 at 30 %, 8-bit
+    // 4.0 / 3.85, the four launches of a 2049 / 5506 layer 19.7 / 18.5.  What the branch costs where nothing is left: the four
+    // launches of a 4096 / 11008 layer, 8-bit, 44.1 / 44.2, the same behind the header or with the load out of line.)
+    if (tid < (x_fast ? n % 8u : 0u)) xs[nvec * 8u + tid] = x[nvec * 8u + tid];
     __builtin_amdgcn_sched_barrier(0);      // these loads do not wait for the header: keep them ahead of those that do
 #pragma unroll
     for (int w = 0; w < (int)(ECS_PANEL_HEADER / 4); ++w) {
