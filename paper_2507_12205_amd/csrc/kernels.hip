@@ -652,9 +652,9 @@ struct NoTable {};
 // TM: bit t set = the image holds units of granularity 2 << t somewhere (the residual set is always handled);
 // DB: width of the delta indices in bits; MODE: 0 = a launch that carries one SpMV (nothing of the batch table is
 // compiled in: every instruction on the way to a wavefront's first loads counts, the scalar unit of a compute unit
-// issues one instruction per cycle for all 16 wavefronts), 1 = several SpMVs, 2 = several SpMVs with the buffer
-// depths that suit many workgroups per compute unit (residual-only images: deeper buffers; one block set: everything
-// requested before the first barrier), 3 = one SpMV with four or eight right-hand sides whose residual chunks are taken in
+// issues one instruction per cycle for all 16 wavefronts), 1 = several SpMVs, 2 = several SpMVs whose panels have many chunks
+// (residual-only images: two buffers) or few (one block set: everything requested before the first barrier; the lines
+// are in launch_tm), 3 = one SpMV with four or eight right-hand sides whose residual chunks are taken in
 // phases (a mode of its own: the loop over phases costs launches that need one phase only 2-9 %, two vectors on
 // 16384 x 1024, 4-bit 6.5 us without it and 7.1 with it, 768 x 768 with four 3.56 and 3.76);
 // K: 16-byte pieces of [tables | x] each thread brings to LDS before the generic loop takes the rest;
@@ -774,12 +774,11 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     BlockSet<4, DB, wide ? 1 : D4, NB, VW, straight> b4;
     BlockSet<2, DB, wide ? 2 : tight ? 1 : D2, NB, VW, straight> b2;
     ResidualSet<DB, (NB > 1) ? 1 : wide ? 2 : (TM == 0 && BATCH ? DR0B : DR), TM == 0 && BATCH, NB, VW> rs;
-    // A launch of an image with block sets that shares its compute units with few others requests the residual set's
-    // first chunks only after the barrier: a wavefront cannot pass the barrier before its requests are out, with every
+    // A launch of an image with block sets requests the residual set's first chunks only after the barrier: a wavefront cannot pass the barrier before its requests are out, with every
     // set requested up front the whole panel is on its way before anything is computed, and the block sets' first
     // chunks are computed while the residual chunk travels (run_first).  Measured: 3-5 % of a lone launch with one
-    // block set, 2 % of a step (7 % of a 5120 x 5120 launch) with two, 6 % with three; with many workgroups per
-    // compute unit (MODE 2) requesting everything first is the faster order.  Several right-hand sides the same (4 % of a
+    // block set, 2 % of a step (7 % of a 5120 x 5120 launch) with two, 6 % with three; with one block set and few chunks
+    // in several matrices (MODE 2) requesting everything first is the faster order.  Several right-hand sides the same (4 % of a
     // launch with two on 4096 x 11008 at 8 bits, FP32 4096 x 4096 at 8 bits 8.55 -> 7.97 us with two, at 4 bits 9.12 -> 8.49
     // with four), but with two right-hand sides and one block set the residual set is better under way (16384 x 1024,
     // 4-bit 6.75 -> 6.27 us, FP32 4096 x 4096, 4-bit 8.18 -> 7.51).  FP32 values,
@@ -843,8 +842,10 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // wavefront's part of X is in LDS: loads return in the order they were requested, so what of X comes late (a wide X, the
     // wavefronts that start last) would queue behind everyone's chunks, and nothing is computed before all of X is there.  us, chunks
     // first / X first: two, 5120 x 5120 at 30 %, 8-bit 6.56 / 6.21, 2048 x 8192 at 40 %, 8-bit 8.15 / 7.77, FP32 4096 x 4096 at 30 % 6.37 /
-    // 5.71; four, 5120 x 13824 at 30 % 14.38 / 13.65, FP32 4096 x 4096 7.20 / 6.62; eight, 5120 x 5120 at 30 % 9.56 / 9.05; a launch that
-    // leaves most of the chip idle the other way round, 48 panels of 768 x 768 with 8-bit deltas, two, 3.53 / 3.69.
+    // 5.71; four, 5120 x 13824 at 30 % 14.38 / 13.65, FP32 4096 x 4096 7.20 / 6.62; eight, 5120 x 5120 at 30 % 9.56 / 9.05.  (All with four
+    // pieces per thread.  Small launches with the number they need: 48 panels of 768 x 768 at 50 %, 8-bit, two 3.31 / 3.29, four 3.55 / 3.52,
+    // eight 4.17 / 4.29; 64 of 1024 x 1024 at 30 %, two 2.81 / 2.85; 256 of 16384 x 1024 at 30 %, two 4.95 / 4.62, four 5.24 / 4.87; before both
+    // changes 3.53, 3.79, 4.52, 3.09, 5.42, 5.74.)
     uint32_t dealt = 0;
     auto request_first = [&]() {
         if constexpr ((TM & 8) != 0) b16.prologue(c, hdr, 3, dealt);
@@ -1216,8 +1217,8 @@ static int launch_m(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
     return (int)s;
 }
 
-// BATCH: the deeper-buffer variant for launches with many workgroups per compute unit; a launch that carries a single
-// SpMV gets the variant with nothing of the batch table compiled in
+// BATCH: the second variant for launches of several SpMVs (launch_tm); a launch that carries a single SpMV gets the variant with
+// nothing of the batch table compiled in
 template <int TM, int DB, bool BATCH, int K, int NB, int VW = 2>
 static int launch_k(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, void *stream)
 {
@@ -1244,8 +1245,11 @@ static int launch_b(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
     if constexpr (VW == 2)
         if (per_thread <= 1) return launch_k<TM, DB, BATCH, 1, 1>(batch, threads, lds_bytes, stream);
     if (per_thread <= 2) return launch_k<TM, DB, BATCH, 2, 1, VW>(batch, threads, lds_bytes, stream);
-    // three: 5120 x 20480 at 20 % 11.04 -> 10.83 us, 4096 x 20480 at 20 %, 8-bit 10.24 -> 10.06; FP32 values gain nothing
-    // (4096 x 11008 15.65 / 15.77, 2048 x 11008 10.63 / 10.73)
+    // Three, us by the variant for four / for three: alone 5120 x 20480 at 20 % 11.09 / 11.00, 2048 x 20480 8.40 / 8.16, 3000 x 22001 at
+    // 15 %, 8-bit 7.85 / 7.66, 2048 x 10240 at 12 %, 8-bit 5.14 / 5.02, 8192 x 18000 at 10 % 9.41 / 9.51; several, 5 x 4096 x 4096 at 15 %
+    // 8.28 / 7.99, 3 x 4096 x 8192 at 50 %, 8-bit 26.80 / 25.99, 16 x 1024 x 4096 17.51 / 17.17, 4 x 2048 x 8192 at 40 % 12.92 / 12.74 and, two
+    // buffers, 4 x 2880 x 10240 at 35 % 18.7 / 18.3, 3 x 4096 x 9000 17.2 / 17.1, 3 x 4096 x 11008 at 30 % 18.0 / 18.0.  FP32 values
+    // gain nothing (4096 x 11008 15.65 / 15.77, 2048 x 11008 10.63 / 10.73).
     if constexpr (VW == 2)
         if (per_thread <= 3) return launch_k<TM, DB, BATCH, 3, 1>(batch, threads, lds_bytes, stream);
     return launch_k<TM, DB, BATCH, 4, 1, VW>(batch, threads, lds_bytes, stream);
@@ -1265,15 +1269,20 @@ static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes
     if (delta_bits == 16) return launch_k<TM, 16, false, 4, 1>(batch, threads, lds_bytes, stream);
     // Residual-only images and images with one block set have a second variant for launches that carry several SpMVs.  The
     // residual-only one (two buffers) keeps more on the way, which pays where a wavefront has many chunks to go through and
-    // the launch is more than one round: us with one / two buffers, 3 x 11008 x 4096 at 30 % (52 chunks a panel) 18.30 / 17.87, 4 x
-    // 5120 x 13824 (79) 35.8 / 33.3, 4 x 8192 x 8192, 8-bit (77) 38.0 / 37.1; but 3 x 8192 x 4096 (39) 13.55 / 14.43, 8 x 2048 x 2048 at 20 % (7)
-    // 5.5 / 6.2, 8 x 4096 x 4096 at 30 %, 8-bit (19) 20.6 / 21.8, and 2 x 13824 x 5120 (80, 512 workgroups) 18.66 / 18.93.
-    // The one-block-set one requests every set before the first barrier, which pays where a wavefront has little more than that:
-    // us with the residual set after the barrier / before it, 3 x 768 x 768 at 30 %, 8-bit (5) 3.39 / 3.29, 4 x 512 x 512 at 50 % (5) 3.37 / 3.27, 8 x
-    // 2048 x 512 (5) 4.94 / 4.86; 16 x 768 x 768 (8) 4.86 / 4.85; but 16 x 1408 x 1408 at 30 %, 8-bit (9.4) 6.66 / 6.78, at 50 % (15) 8.92 / 9.14, 8 x 600 x
-    // 1700 (18) 4.96 / 5.17, 2 x 4096 x 4096 (43) 8.97 / 9.39.
+    // the launch is more than one round: us with one / two buffers, 3 x 8192 x 4800 at 30 % (45.4 chunks a panel) 16.1 / 15.7, 3 x 11008 x 4096
+    // (52) 18.6 / 18.1, 3 x 2880 x 16384 (77, 540 workgroups) 25.1 / 23.4, 4 x 5120 x 13824 (79) 35.8 / 33.3, 4 x 8192 x 8192, 8-bit (77)
+    // 38.0 / 37.1; but 3 x 11008 x 4096 at 25 % (43.9) 15.6 / 15.7, 3 x 8192 x 4096 (39) 13.5 / 14.4, 8 x 2048 x 2048 at 20 % (7) 5.5 / 6.2,
+    // 8 x 4096 x 4096 at 30 %, 8-bit (19) 20.6 / 21.8, and 2 x 13824 x 5120 (80, 512 workgroups) 18.1 / 18.3, 3 x 2640 x 20000 (79, 495)
+    // 18.7 / 18.9.
+    // The one-block-set one requests every set before the first barrier, which pays where a wavefront has little more than that, less
+    // so the more workgroups a compute unit holds.  us with the residual set after the barrier / before it: 4 x 2048 x 300 at
+    // 50 % (3 chunks a panel, 512 workgroups) 4.11 / 3.84, 8 x 4096 x 300 (3, 2048) 6.41 / 6.01, 16 x 1024 x 600 (6.2, 1024) 4.96 / 4.91, 8 x
+    // 4096 x 500 (5.2, 2048) 6.64 / 6.58; up to 9 chunks 3 x 768 x 1100 at 30 %, 8-bit (7.1, 144) 3.62 / 3.46, 4 x 1024 x 800 (8.4, 256)
+    // 3.99 / 3.79, 8 x 1024 x 1250, 8-bit (8.3, 512) 4.59 / 4.48, but from 1024 workgroups on 16 x 1024 x 800 (8.4, 1024) 5.51 / 5.63, 8 x 4096 x
+    // 700 (7.3, 2048) 7.44 / 7.65; and beyond 8 x 1024 x 900 (9.3, 512) 4.84 / 4.90, 16 x 1408 x 1408, 8-bit (9.4) 6.66 / 6.78, at 50 % (15)
+    // 8.92 / 9.14, 8 x 600 x 1700 (18) 4.96 / 5.17, 2 x 4096 x 4096 (43) 8.97 / 9.39.
     const uint64_t grid = batch.item[batch.count - 1].block_end;
-    const bool second = TM == 0 ? grid > 512u && chunks > 45u * grid : TM == 1 && chunks <= 9u * grid;
+    const bool second = TM == 0 ? grid > 512u && chunks > 45u * grid : TM == 1 && chunks <= (grid < 1024u ? 9u : 6u) * grid;
     if (batch.count > 1 && second)
         return delta_bits == 4 ? launch_b<TM, 4, TM <= 1>(batch, threads, lds_bytes, stream)
                                : launch_b<TM, 8, TM <= 1>(batch, threads, lds_bytes, stream);

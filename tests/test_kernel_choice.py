@@ -1,0 +1,105 @@
+"""Which kernel a launch takes, on both sides of every line: the variants for several matrices, the staging variants (16-byte pieces of
+tables and x per thread), phases, and the widths of deltas and values."""
+import batch_cases
+import pytest
+import standin
+
+HEAD = r"""
+import re
+fake.fake_name_kernels()
+X, Y = 0x200000, 0x300000
+def upload(W, **o):
+    f32 = W.dtype == np.float32
+    A = (B.ecspmv_build_dense_f32 if f32 else B.ecspmv_build_dense)(W, B.make_opts(**o))
+    A.ecspmv_upload(0x100000, A.ecspmv_device_bytes(), 0)
+    return A
+def kernel():
+    return [int(v) for v in re.findall(r"Li(\d+)E", re.search(r"ecspmv_kernelI((?:Li\d+E){6})E", fake.fake_kernel().decode()).group(1))]
+"""
+
+BATCH = HEAD + r"""
+import batch_cases as C
+out = []
+for c in arg:
+    mats = [upload(C.matrix(c, k), **C.options(c)) for k in range(c["count"])]
+    B.ecspmv_run_batch(mats, [X + 2 * (k % 2) for k in range(c["count"])], [Y] * c["count"], 0)
+    st = [A.ecspmv_stats() for A in mats]
+    out.append(dict(kernel=kernel(), grid=fake.fake_launched(GRID), chunks=sum(C.chunks(s) for s in st) / sum(s.num_panels for s in st),
+                    sets=[int(any(s.units_by_g[g] for s in st)) for g in range(1, 5)]))
+print(json.dumps(out))
+"""
+
+
+@pytest.mark.parametrize("cases", [batch_cases.RESIDUAL, batch_cases.ONE_SET], ids=["residual", "one_set"])
+def test_several_matrices(tmp_path, cases):
+    for c, got in zip(cases, standin.run(tmp_path, BATCH, cases)):
+        tm, mode, k = c["kernel"]
+        assert c["chunks"][0] <= got["chunks"] <= c["chunks"][1], (c, got)           # the case is what it says
+        assert got["grid"] == c["panels"] * c["count"] and got["sets"] == [tm, 0, 0, 0], (c, got)
+        assert got["kernel"] == [tm, c["bits"], mode, k, 1, 2], (c, got)
+
+
+PIECES = HEAD + r"""
+def build(c, n):
+    rng = np.random.default_rng(n)
+    W = np.where(rng.random((c["rows"], n)) < c["density"], np.float16(0.5), np.float16(0)).astype(np.float32 if c["fp32"] else np.float16)
+    return upload(W, max_granularity=1, delta_bits=c["bits"], num_panels=1, threads_per_wg=c["threads"])
+out = []
+for c in arg:
+    vw, nb = 4 if c["fp32"] else 2, c["nb"]
+    def pieces(n, x=True):
+        return build(c, n).ecspmv_stats().meta_stride // 16 + (n * nb * vw // 16 if x else 0)
+    def run(n, x):
+        A = build(c, n)
+        A.ecspmv_run_multi(x, Y, nb, 0) if nb > 1 else A.ecspmv_run(x, Y, 0)
+        return kernel()
+    lo, hi = 1, 8 * c["pieces"]                          # the widest that needs no more than `pieces`, and one that needs more
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if pieces(mid) <= c["pieces"] else (lo, mid)
+    widths = range(max(1, lo - 8), lo + 9)
+    below, above = max((n for n in widths if pieces(n) <= c["pieces"]), key=pieces), min((n for n in widths if pieces(n) > c["pieces"]), key=pieces)
+    out.append(dict(below=run(below, X), above=run(above, X), at=[pieces(below), pieces(above)], unaligned=run(above, X + vw),
+                    tables=pieces(above, False)))
+print(json.dumps(out))
+"""
+
+
+@pytest.mark.parametrize("nb,fp32", [(1, False), (1, True), (2, False), (4, False), (8, False), (2, True), (4, True)])
+def test_pieces_per_thread(tmp_path, nb, fp32):
+    threads = 128
+    cases = [dict(nb=nb, fp32=fp32, bits=bits, threads=threads, rows=8, density=0.1, pieces=k * threads) for bits in (4, 8) for k in (1, 2, 3)]
+
+    def variant(per_thread):
+        if nb == 1 and fp32:
+            return 2 if per_thread <= 2 else 4
+        return min(per_thread, 4)
+    for c, got in zip(cases, standin.run(tmp_path, PIECES, cases)):
+        k = c["pieces"] // threads
+        assert got["at"][0] <= c["pieces"] < got["at"][1] and c["pieces"] - got["at"][0] <= 1 and got["at"][1] - c["pieces"] <= 3, (c, got)
+        tail = [nb, 4 if fp32 else 2]
+        assert got["below"] == [0, c["bits"], 0, variant(k), *tail], (c, got)
+        assert got["above"] == [0, c["bits"], 0, variant(k + 1), *tail], (c, got)
+        assert got["unaligned"] == [0, c["bits"], 0, variant(-(-got["tables"] // threads)), *tail], (c, got)   # x comes value by value
+
+
+PHASES = HEAD + r"""
+out = []
+for c in arg:
+    rng = np.random.default_rng(1)
+    W = np.where(rng.random((c["rows"], c["n"])) < c["density"], np.float16(0.5), np.float16(0))
+    A = upload(W, max_granularity=1, delta_bits=4, num_panels=1)
+    A.ecspmv_run_multi(X, Y, c["nb"], 0)
+    out.append(dict(kernel=kernel(), grid=fake.fake_launched(GRID), lds=fake.fake_launched(LDS)))
+print(json.dumps(out))
+"""
+
+
+def test_phases(tmp_path):
+    """eight right-hand sides whose partial sums fit LDS beside X, do not, and whose X does not fit: half the columns a workgroup"""
+    cases = [dict(rows=16, n=1000, density=0.5, nb=8), dict(rows=100, n=1000, density=0.9, nb=8), dict(rows=16, n=10300, density=0.2, nb=8)]
+    one, phases, split = standin.run(tmp_path, PHASES, cases)
+    assert one["kernel"][:3] == [0, 4, 0] and one["kernel"][4:] == [8, 2] and one["grid"] == 1
+    assert phases["kernel"] == [0, 4, 3, 4, 8, 2] and phases["grid"] == 1
+    assert split["kernel"][2] in (0, 3) and split["kernel"][4:] == [4, 2] and split["grid"] == 2
+    assert all(g["lds"] <= 160 * 1024 for g in (one, phases, split))
