@@ -1,9 +1,10 @@
 """Launches of several matrices at both sides of the lines between their two kernel variants (two residual buffers; every set
 requested before the first barrier): y has the bits of lone launches and stays in the oracle's band, with x that ends in a whole
-16-byte piece and not."""
+16-byte piece and not, one image for all items, and items with a matrix of their own."""
 import numpy as np
 import pytest
 
+import batch_cases
 from workloads import generators as gen
 from test_gpu_multi import E  # noqa: F401  -- the fixture
 from test_gpu_workgroup_size import bits, in_band, upload
@@ -40,3 +41,27 @@ def test_both_variants(E, m, n, density, panels, count, g, chunks, delta_bits): 
         E.device.run(A, xs[k], z)
         assert torch.equal(bits(ys[k]), bits(z)), k
     assert in_band(ys[0], W, xs[0])
+
+
+# every item narrower than the one before it, every second x off a 16-byte boundary, with the two kernel variants and all four
+# staging variants of the second one
+@pytest.mark.parametrize("c", batch_cases.CASES, ids=lambda c: "{kernel}-{count}x{panels}x{rows}x{n}-d{bits}".format(**c).replace(" ", ""))
+def test_unequal_matrices(E, c):  # noqa: F811
+    import torch
+    print(f"[case] {c}", flush=True)
+    count, m = c["count"], c["rows"] * c["panels"]
+    Ws = [batch_cases.matrix(c, k) for k in range(count)]
+    mats = [upload(E, W, **batch_cases.options(c)) for W in Ws]
+    st = [A.ecspmv_stats() for A in mats]
+    assert c["chunks"][0] < sum(map(batch_cases.chunks, st)) / sum(s.num_panels for s in st) < c["chunks"][1]
+    xs, ys = [], [torch.full((m,), float("nan"), dtype=torch.float16, device="cuda") for _ in range(count)]
+    for k, W in enumerate(Ws):
+        buf = torch.zeros(W.shape[1] + 1, dtype=torch.float16, device="cuda")
+        x = buf[k % 2:k % 2 + W.shape[1]]
+        x.copy_(torch.from_numpy(np.random.default_rng(k).standard_normal(W.shape[1]).astype(np.float32)).cuda())
+        xs.append(x)
+    E.ecspmv_run_batch(mats, [x.data_ptr() for x in xs], [y.data_ptr() for y in ys], E.device._stream_handle())
+    z = torch.empty(m, dtype=torch.float16, device="cuda")
+    for A, W, x, y in zip(mats, Ws, xs, ys):
+        E.device.run(A, x, z)
+        assert torch.equal(bits(y), bits(z)) and in_band(y, W, x)
