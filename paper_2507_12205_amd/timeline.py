@@ -46,6 +46,49 @@ STAMPS = [
 ]
 
 
+def placed(T, mhz):
+    """Stamps [launches, workgroups, wavefronts, 8] of one point as microseconds after the launch's first wavefront started: when every
+    wavefront started, passed the point, ended; and the constant-rate clock at the first start and the last end of every launch."""
+    valid = T[..., 0] > 0
+    # The stamp counter is not the same on every part of the chip; the constant-rate counter is.  Every wavefront's
+    # stamps are therefore placed on the constant-rate axis through its own pair (start stamp, constant-rate start);
+    # differences are taken in integers first.
+    real0 = np.where(valid, T[..., 3], np.iinfo(np.int64).max).min(axis=(1, 2))              # per launch
+    start = (T[..., 3] - real0[:, None, None]).astype(np.float64) * 0.01                     # us
+    at = start + (T[..., 1] - T[..., 0]).astype(np.float64) / mhz
+    end = start + (T[..., 2] - T[..., 0]).astype(np.float64) / mhz
+    last_real = np.where(valid, T[..., 4], 0).max(axis=(1, 2))
+    return start, at, end, real0, last_real
+
+
+def rows_of(k, label, T, mhz, first):
+    """The table's row of point k, from the launches that stamped it (the first launch left out); with `first` the row of the
+    wavefronts' start before it, from the same launches.  Every point is stamped in launches of its own, so two rows compare only as far as
+    launches do; `own_start_median_us` is when the wavefronts that passed the point had started in these very launches, and
+    `before_own_start` how many passed it before they had."""
+    start, at, _, _, _ = placed(T, mhz)
+    valid = T[..., 0] > 0
+    ok = valid & (T[..., 1] > 0)
+    use = [r for r in range(1, len(T)) if ok[r].any()]
+    if not use:
+        return []
+
+    def mean(values):
+        return round(float(np.mean(values)), 3)
+    rows = []
+    if first:
+        rows.append(dict(stamp=0, label=STAMPS[0][1], first_us=0.0, median_us=mean([np.median(start[r][valid[r]]) for r in use]),
+                         last_us=mean([start[r][valid[r]].max() for r in use]),
+                         last_wave_of_wg_median_us=mean([np.median(start[r].max(axis=1)) for r in use])))
+    # the slowest wavefront of a workgroup is the one a barrier waits for
+    rows.append(dict(stamp=k, label=label, first_us=mean([at[r][ok[r]].min() for r in use]),
+                     median_us=mean([np.median(at[r][ok[r]]) for r in use]), last_us=mean([at[r][ok[r]].max() for r in use]),
+                     last_wave_of_wg_median_us=mean([np.median(np.where(ok[r], at[r], -np.inf).max(axis=1)) for r in use]),
+                     own_start_median_us=mean([np.median(start[r][ok[r]]) for r in use]),
+                     before_own_start=int(sum((at[r] < start[r])[ok[r]].sum() for r in use)), wavefronts=int(ok[use].sum() // len(use))))
+    return rows
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--config", type=int, default=3)
@@ -139,32 +182,13 @@ def main():
             d_real = (T[..., 4] - T[..., 3])[valid].astype(np.float64)
             d_clk = (T[..., 2] - T[..., 0])[valid].astype(np.float64)
             mhz = float(d_clk.sum() / d_real.sum() * 100.0)
-        # The stamp counter is not the same on every part of the chip; the constant-rate counter is.  Every wavefront's
-        # stamps are therefore placed on the constant-rate axis through its own pair (start stamp, constant-rate start);
-        # differences are taken in integers first.
-        real0 = np.where(valid, T[..., 3], np.iinfo(np.int64).max).min(axis=(1, 2))              # per launch
-        start = (T[..., 3] - real0[:, None, None]).astype(np.float64) * 0.01                     # us
-        at = start + (T[..., 1] - T[..., 0]).astype(np.float64) / mhz
-        end = start + (T[..., 2] - T[..., 0]).astype(np.float64) / mhz
-        ok = valid & (T[..., 1] > 0)
-        use = [r for r in range(1, R) if ok[r].any()]
-        if not use:
+        more = rows_of(k, label, T, mhz, first=not rows)
+        if not more:
             continue
-        if not rows:
-            rows.append(dict(stamp=0, label=STAMPS[0][1],
-                             first_us=0.0, median_us=round(float(np.mean([np.median(start[r][valid[r]]) for r in use])), 3),
-                             last_us=round(float(np.mean([start[r][valid[r]].max() for r in use])), 3),
-                             last_wave_of_wg_median_us=round(float(np.mean([np.median(start[r].max(axis=1)) for r in use])), 3)))
-        # the slowest wavefront of a workgroup is the one a barrier waits for
-        wg_last = [np.median(np.where(ok[r], at[r], -np.inf).max(axis=1)) for r in use]
-        rows.append(dict(stamp=k, label=label, first_us=round(float(np.mean([at[r][ok[r]].min() for r in use])), 3),
-                         median_us=round(float(np.mean([np.median(at[r][ok[r]]) for r in use])), 3),
-                         last_us=round(float(np.mean([at[r][ok[r]].max() for r in use])), 3),
-                         last_wave_of_wg_median_us=round(float(np.mean(wg_last)), 3),
-                         wavefronts=int(ok[use].sum() // len(use))))
-        span = float(np.mean([np.where(valid[r], end[r], -np.inf).max() for r in use]))
+        rows += more
+        end, real0, last_real = placed(T, mhz)[2:]
+        span = float(np.mean([end[r][T[r, ..., 0] > 0].max() for r in range(1, R) if (T[r, ..., 1] > 0).any()]))
         # from the last instruction of a launch to the first of the next, on the constant-rate clock
-        last_real = np.where(valid, T[..., 4], 0).max(axis=(1, 2))
         gap = float(np.mean((real0[1:] - last_real[:-1])[1:]) * 0.01)
     if args.raw:
         np.savez_compressed(args.raw, **{f"stamp{k}": v for k, v in raw.items()})

@@ -7,13 +7,25 @@ import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
-pytestmark = pytest.mark.gpu
+from paper_2507_12205_amd import timeline
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
+def assert_in_order(by):
+    """Every wavefront passes every point after it started, in the launches that stamped the point.  From one point to another launches
+    differ, so only points that lie hundreds of nanoseconds apart are compared: header here, first barrier, second barrier."""
+    for k, row in by.items():
+        if k:
+            assert row["before_own_start"] == 0 and row["own_start_median_us"] <= row["median_us"], row
+    med = [by[k]["median_us"] for k in (23, 1, 4, 12)]
+    assert all(a <= b for a, b in zip(med, med[1:])), med
+
+
+@pytest.mark.gpu
 def test_timeline_runs_and_points_come_in_order(tmp_path):
     from paper_2507_12205_amd import build as B
     if not os.path.exists(B.TRACE_LIB):
@@ -29,9 +41,29 @@ def test_timeline_runs_and_points_come_in_order(tmp_path):
     by = {row["stamp"]: row for row in d["stamps"]}
     for k in (0, 1, 2, 3, 4, 12):
         assert k in by, f"stamp {k} missing"
-    # a wavefront passes these points in this order, so their medians over a launch do too
-    order = [0, 23, 1, 4, 12]
-    med = [by[k]["median_us"] for k in order]
-    assert all(a <= b for a, b in zip(med, med[1:])), med
+    assert_in_order(by)
     assert 0.0 < d["kernel_span_us"] < 100.0 and d["us_per_launch_stamps_off"] > 0.0
     assert 500.0 < d["stamp_clock_mhz"] < 3000.0
+
+
+def stamps(starts, passed):
+    """a launch of one workgroup per entry: clock at the start, at the point and at the end, constant-rate clock at start and end"""
+    T = np.zeros((2, len(starts), 1, 8), dtype=np.int64)
+    for i, s in enumerate(starts):
+        clock, real = 10 ** 9 + 7 * i, 5000 + s                        # 2000 MHz and 100 MHz
+        T[:, i, 0, :5] = clock, clock + passed, clock + 4000, real, real + 200
+    return T
+
+
+def test_order_does_not_depend_on_when_launches_start():
+    """a launch whose wavefronts start sooner than those of the launch the start was taken from: every wavefront is in order, the medians
+    of two launches are not; and a wavefront that passes a point before it started is found"""
+    early, late, by = [0, 10, 20], [0, 23, 40], {}
+    for k, starts, passed in ((22, late, 4), (23, early, 6), (1, late, 600), (4, early, 1500), (12, late, 3000)):
+        for row in timeline.rows_of(k, str(k), stamps(starts, passed), 2000.0, first=not by):
+            by[row["stamp"]] = row
+    assert by[0]["median_us"] > by[23]["median_us"]
+    assert_in_order(by)
+    [row] = timeline.rows_of(23, "23", stamps(early, -1), 2000.0, first=False)
+    with pytest.raises(AssertionError):
+        assert_in_order({**by, 23: row})
