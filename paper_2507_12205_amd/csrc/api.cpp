@@ -374,7 +374,7 @@ int ecspmv_run_batch(const ecspmv_matrix *const *As, const void *const *d_xs, vo
         std::memset(&b, 0, offsetof(ecs::EcsBatch, item) + sizeof(ecs::EcsBatchItem) * (size_t)(nb == 1 ? 1 : ECS_MAX_BATCH));
         b.count = (uint32_t)nb;
         uint32_t blocks = 0, lds = 0, mask = 0, pieces = 0, rows = 0;
-        uint64_t chunks = 0;
+        uint64_t chunks = 0, block_chunks = 0;
         for (int32_t i = 0; i < nb; ++i) {
             const int32_t src = base + i;
             const ecs::Image &im = As[src]->image;
@@ -391,6 +391,7 @@ int ecspmv_run_batch(const ecspmv_matrix *const *As, const void *const *d_xs, vo
             lds = im.lds_bytes > lds ? im.lds_bytes : lds;
             mask |= im.type_mask;
             chunks += im.total_chunks;
+            block_chunks += im.block_chunks;
             pieces = std::max(pieces, (im.meta_stride + it.x_bytes) / 16u);
             rows = std::max(rows, (uint32_t)((im.m + im.num_panels - 1) / im.num_panels));
         }
@@ -400,7 +401,7 @@ int ecspmv_run_batch(const ecspmv_matrix *const *As, const void *const *d_xs, vo
             const int t = As[base + i]->image.threads_per_wg;
             if (t) threads = (uint32_t)t;                      // a build-time choice overrides
         }
-        int s = hip_status(ecs::launch_ecspmv(b, threads, lds, mask, (uint32_t)bits, (uint32_t)vbits, chunks, stream));
+        int s = hip_status(ecs::launch_ecspmv(b, threads, lds, mask, (uint32_t)bits, (uint32_t)vbits, chunks, block_chunks, stream));
         if (s) return s;
     }
     return ECSPMV_OK;

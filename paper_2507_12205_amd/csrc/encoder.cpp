@@ -1044,7 +1044,7 @@ int build_image(const Source &A, const BuildParams &bp, Image &out)
     }
     uint32_t stride = 256, meta = 16, slots = 1;
     out.max_block_slots = out.max_chunks = 0;
-    out.total_chunks = 0;
+    out.total_chunks = out.block_chunks = 0;
     for (auto &lay : lays) {
         if (lay.err) return lay.err;
         if (lay.bytes > 0xFFFFF000ull) return -2;                            // offsets inside a panel are 32-bit
@@ -1054,8 +1054,9 @@ int build_image(const Source &A, const BuildParams &bp, Image &out)
         out.max_block_slots = std::max(out.max_block_slots, lay.nslots);
         out.max_chunks = std::max(out.max_chunks, lay.nchunks);
         out.total_chunks += lay.nchunks;
-        for (int t = 1; t <= ECS_NUM_BTYPES; ++t) out.total_chunks += (uint64_t)(lay.units_by_g[t] + 3) / 4;
+        for (int t = 1; t <= ECS_NUM_BTYPES; ++t) out.block_chunks += (uint64_t)(lay.units_by_g[t] + 3) / 4;
     }
+    out.total_chunks += out.block_chunks;
     meta = align_up(meta, 16);
     // 4 KB of zeros after the last panel: loads that stand in for missing chunks may run past a short last panel
     const uint64_t total = ECS_IMAGE_HEADER + (uint64_t)stride * (uint64_t)P + 4096u;

@@ -92,7 +92,7 @@ struct Image {
     int num_panels = 0, threads_per_wg = 1024, delta_bits = 8, value_bits = 16;
     uint32_t panel_stride = 0, meta_stride = 0, max_slots = 0, lds_bytes = 0;
     uint32_t max_block_slots = 0, max_chunks = 0;      // over the panels: slots of the block sets, residual chunks
-    uint64_t total_chunks = 0;                         // what a wavefront takes at a time (64 lane units, 4 units), all panels
+    uint64_t total_chunks = 0, block_chunks = 0;       // what a wavefront takes at a time (64 lane units, 4 units), all panels; those of units
     uint32_t type_mask = 0;   // bit t set: some panel holds units of granularity 2 << t
     ecspmv_stats_t stats;
 };

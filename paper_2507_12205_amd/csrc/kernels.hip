@@ -653,8 +653,8 @@ struct NoTable {};
 // DB: width of the delta indices in bits; MODE: 0 = a launch that carries one SpMV (nothing of the batch table is
 // compiled in: every instruction on the way to a wavefront's first loads counts, the scalar unit of a compute unit
 // issues one instruction per cycle for all 16 wavefronts), 1 = several SpMVs, 2 = several SpMVs whose panels have many chunks
-// (residual-only images: two buffers) or few (one block set: everything requested before the first barrier; the lines
-// are in launch_tm), 3 = one SpMV with four or eight right-hand sides whose residual chunks are taken in
+// (residual-only images: two buffers) or few block units (one block set: everything requested before the first barrier; the
+// lines are in launch_tm), 3 = one SpMV with four or eight right-hand sides whose residual chunks are taken in
 // phases (a mode of its own: the loop over phases costs launches that need one phase only 2-9 %, two vectors on
 // 16384 x 1024, 4-bit 6.5 us without it and 7.1 with it, 768 x 768 with four 3.56 and 3.76);
 // K: 16-byte pieces of [tables | x] each thread brings to LDS before the generic loop takes the rest;
@@ -777,8 +777,8 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // A launch of an image with block sets requests the residual set's first chunks only after the barrier: a wavefront cannot pass the barrier before its requests are out, with every
     // set requested up front the whole panel is on its way before anything is computed, and the block sets' first
     // chunks are computed while the residual chunk travels (run_first).  Measured: 3-5 % of a lone launch with one
-    // block set, 2 % of a step (7 % of a 5120 x 5120 launch) with two, 6 % with three; with one block set and few chunks
-    // in several matrices (MODE 2) requesting everything first is the faster order.  Several right-hand sides the same (4 % of a
+    // block set, 2 % of a step (7 % of a 5120 x 5120 launch) with two, 6 % with three; with one block set and few block
+    // units in several matrices (MODE 2) requesting everything first is the faster order.  Several right-hand sides the same (4 % of a
     // launch with two on 4096 x 11008 at 8 bits, FP32 4096 x 4096 at 8 bits 8.55 -> 7.97 us with two, at 4 bits 9.12 -> 8.49
     // with four), but with two right-hand sides and one block set the residual set is better under way (16384 x 1024,
     // 4-bit 6.75 -> 6.27 us, FP32 4096 x 4096, 4-bit 8.18 -> 7.51).  FP32 values,
@@ -841,11 +841,12 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // anything is computed and before the tables and x have even reached LDS.  With several right-hand sides only once this
     // wavefront's part of X is in LDS: loads return in the order they were requested, so what of X comes late (a wide X, the
     // wavefronts that start last) would queue behind everyone's chunks, and nothing is computed before all of X is there.  us, chunks
-    // first / X first: two, 5120 x 5120 at 30 %, 8-bit 6.56 / 6.21, 2048 x 8192 at 40 %, 8-bit 8.15 / 7.77, FP32 4096 x 4096 at 30 % 6.37 /
-    // 5.71; four, 5120 x 13824 at 30 % 14.38 / 13.65, FP32 4096 x 4096 7.20 / 6.62; eight, 5120 x 5120 at 30 % 9.56 / 9.05.  (All with four
-    // pieces per thread.  Small launches with the number they need: 48 panels of 768 x 768 at 50 %, 8-bit, two 3.31 / 3.29, four 3.55 / 3.52,
-    // eight 4.17 / 4.29; 64 of 1024 x 1024 at 30 %, two 2.81 / 2.85; 256 of 16384 x 1024 at 30 %, two 4.95 / 4.62, four 5.24 / 4.87; before both
-    // changes 3.53, 3.79, 4.52, 3.09, 5.42, 5.74.)
+    // first / X first: two, 5120 x 5120 at 30 %, 8-bit 6.56 / 6.21, 2048 x 8192 at 40 %, 8-bit 8.15 / 7.77, 16384 x 1024 at 30 % 4.95 / 4.62;
+    // four 5.24 / 4.87, 5120 x 13824 at 30 % 14.38 / 13.65, FP32 4096 x 4096 7.20 / 6.62; eight, 5120 x 5120 at 30 % 9.56 / 9.05.  Over 984
+    // launches X first is 3.5 % faster with sixteen wavefronts, at every width of X and number of chunks, and 1.5 % slower with eight (two,
+    // 256 panels of 4096 x 2048 at 20 %, FP32 3.26 / 3.35, 8192 x 3000 at 10 % 4.36 / 4.60; four, 1024 x 1024 at 30 % 2.92 / 3.04; 48
+    // panels of 768 x 768 at 50 %, 8-bit, two 3.31 / 3.29, eight 4.17 / 4.29).  Both orders in one kernel, by the workgroup size, were
+    // measured and not kept: the waits then count the loads of either, 6 % slower with eight wavefronts.
     uint32_t dealt = 0;
     auto request_first = [&]() {
         if constexpr ((TM & 8) != 0) b16.prologue(c, hdr, 3, dealt);
@@ -1257,7 +1258,7 @@ static int launch_b(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
 
 template <int TM>
 static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, uint32_t delta_bits, uint32_t value_bits,
-                     uint64_t chunks, void *stream)
+                     uint64_t chunks, uint64_t block_chunks, void *stream)
 {
     // FP32 values: lone-launch buffer depths
     if (value_bits == 32) {
@@ -1274,15 +1275,15 @@ static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes
     // 38.0 / 37.1; but 3 x 11008 x 4096 at 25 % (43.9) 15.6 / 15.7, 3 x 8192 x 4096 (39) 13.5 / 14.4, 8 x 2048 x 2048 at 20 % (7) 5.5 / 6.2,
     // 8 x 4096 x 4096 at 30 %, 8-bit (19) 20.6 / 21.8, and 2 x 13824 x 5120 (80, 512 workgroups) 18.1 / 18.3, 3 x 2640 x 20000 (79, 495)
     // 18.7 / 18.9.
-    // The one-block-set one requests every set before the first barrier, which pays where a wavefront has little more than that, less
-    // so the more workgroups a compute unit holds.  us with the residual set after the barrier / before it: 4 x 2048 x 300 at
-    // 50 % (3 chunks a panel, 512 workgroups) 4.11 / 3.84, 8 x 4096 x 300 (3, 2048) 6.41 / 6.01, 16 x 1024 x 600 (6.2, 1024) 4.96 / 4.91, 8 x
-    // 4096 x 500 (5.2, 2048) 6.64 / 6.58; up to 9 chunks 3 x 768 x 1100 at 30 %, 8-bit (7.1, 144) 3.62 / 3.46, 4 x 1024 x 800 (8.4, 256)
-    // 3.99 / 3.79, 8 x 1024 x 1250, 8-bit (8.3, 512) 4.59 / 4.48, but from 1024 workgroups on 16 x 1024 x 800 (8.4, 1024) 5.51 / 5.63, 8 x 4096 x
-    // 700 (7.3, 2048) 7.44 / 7.65; and beyond 8 x 1024 x 900 (9.3, 512) 4.84 / 4.90, 16 x 1408 x 1408, 8-bit (9.4) 6.66 / 6.78, at 50 % (15)
-    // 8.92 / 9.14, 8 x 600 x 1700 (18) 4.96 / 5.17, 2 x 4096 x 4096 (43) 8.97 / 9.39.
+    // The one-block-set one requests every set before the first barrier, the residual set too, which pays where wavefronts have no
+    // block chunk of their own to compute while the residual chunk travels: up to three block chunks for four wavefronts of a
+    // workgroup, whatever the rest.  Over 644 launches (2 to 16 matrices, 32 to 4096 workgroups, 1 to 60 chunks a panel): up to a quarter
+    // of a block chunk per wavefront it is 2.9 % faster on average, to a half 1.9, to three quarters 0.8, to one 0.4 % slower, to one and
+    // a half 2, to three 3.5.  us with the residual set after the barrier / before it: 8 x 4096 x 300 at 50 % 6.41 / 6.01, 4 x 1024 x 1500 at
+    // 30 %, 8-bit 3.73 / 3.61, 8 x 1024 x 1900 at 42 %, all columns alike 5.79 / 5.63, 4 x 2048 x 2400 6.22 / 6.06; but 16 x 1408 x 1408 at 50 %
+    // 8.92 / 9.14, 8 x 4096 x 800 7.87 / 8.18, 8 x 1024 x 2600 at 30 %, 8-bit 5.11 / 5.44, 2 x 4096 x 4096 at 50 % 8.97 / 9.39.
     const uint64_t grid = batch.item[batch.count - 1].block_end;
-    const bool second = TM == 0 ? grid > 512u && chunks > 45u * grid : TM == 1 && chunks <= (grid < 1024u ? 9u : 6u) * grid;
+    const bool second = TM == 0 ? grid > 512u && chunks > 45u * grid : TM == 1 && 4u * block_chunks <= 3u * grid * (threads / 64u);
     if (batch.count > 1 && second)
         return delta_bits == 4 ? launch_b<TM, 4, TM <= 1>(batch, threads, lds_bytes, stream)
                                : launch_b<TM, 8, TM <= 1>(batch, threads, lds_bytes, stream);
@@ -1351,16 +1352,16 @@ int launch_ecspmv_multi(const EcsBatch &batch, uint32_t threads, uint32_t lds_by
 }
 
 int launch_ecspmv(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, uint32_t type_mask, uint32_t delta_bits,
-                  uint32_t value_bits, uint64_t chunks, void *stream)
+                  uint32_t value_bits, uint64_t chunks, uint64_t block_chunks, void *stream)
 {
     // one instantiation per highest granularity present: sets that do not occur cost no registers
     const int top = (type_mask & 8) ? 15 : (type_mask & 4) ? 7 : (type_mask & 2) ? 3 : (type_mask & 1) ? 1 : 0;
     switch (top) {
-    case 15: return launch_tm<15>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, stream);
-    case 7: return launch_tm<7>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, stream);
-    case 3: return launch_tm<3>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, stream);
-    case 1: return launch_tm<1>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, stream);
-    default: return launch_tm<0>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, stream);
+    case 15: return launch_tm<15>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, block_chunks, stream);
+    case 7: return launch_tm<7>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, block_chunks, stream);
+    case 3: return launch_tm<3>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, block_chunks, stream);
+    case 1: return launch_tm<1>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, block_chunks, stream);
+    default: return launch_tm<0>(batch, threads, lds_bytes, delta_bits, value_bits, chunks, block_chunks, stream);
     }
 }
 

@@ -26,9 +26,9 @@ struct EcsBatch {
 static_assert(sizeof(EcsBatchItem) == 48 && sizeof(EcsBatch) == 16 + 48 * ECS_MAX_BATCH, "layout the kernel reads");
 
 // Launches one kernel for all items (count <= ECS_MAX_BATCH, same workgroup size for all; `chunks`: what a wavefront takes at a
-// time, of all items together).
+// time, of all items together; `block_chunks`: those of block units).
 int launch_ecspmv(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, uint32_t type_mask, uint32_t delta_bits,
-                  uint32_t value_bits, uint64_t chunks, void *stream);
+                  uint32_t value_bits, uint64_t chunks, uint64_t block_chunks, void *stream);
 // One matrix, nb = 2, 4 or 8 columns of X and Y per workgroup, row_stride / nb workgroups per panel (row_stride: values
 // from one row of X, and of Y, to the next); type_mask must not have the bit of the 16-grained set, nor that of the
 // 8-grained set with FP32 values.

@@ -19,16 +19,17 @@ RESIDUAL = (case((0, 2, 1), 3, 176, 18, 2901, 0.95, (46, 60))
             + case((0, 2, 2), 3, 171, 9, 6003, 0.92, (46, 60))               # 513 workgroups
             + case((0, 1, 2), 4, 128, 9, 6003, 0.92, (46, 60))               # 512
             + case((0, 1, 3), 3, 176, 6, 10005, 0.75, (41, 44.9)))           # fewer chunks
-# one block set: every set requested before the first barrier up to 9 chunks a panel, from 1024 workgroups on up to 6
+# one block set: every set requested before the first barrier up to three block chunks for four wavefronts
 ONE_SET = (case((1, 2, 1), 5, 4, 8, 601, 0.3, (3, 8), stride=4)
            + case((1, 2, 2), 5, 4, 4, 6003, 0.05, (4, 8), stride=12, step=7)
            + case((1, 2, 3), 5, 4, 2, 10005, 0.05, (3, 8), stride=12, step=7)
            + case((1, 2, 4), 5, 4, 2, 14007, 0.05, (3, 8), stride=12, step=7)
-           + case((1, 1, 1), 5, 4, 22, 601, 0.3, (9.1, 16), stride=4)
-           + case((1, 1, 2), 5, 4, 8, 6003, 0.05, (9.1, 16), stride=12, step=7)
-           + case((1, 2, 1), 16, 63, 16, 601, 0.3, (6.1, 8), stride=4)       # 1008 workgroups
-           + case((1, 1, 1), 16, 64, 16, 601, 0.3, (6.1, 8), stride=4)       # 1024
-           + case((1, 2, 1), 16, 64, 8, 601, 0.3, (3, 5), stride=4))
+           + case((1, 2, 2), 5, 4, 16, 6003, 0.4, (35, 60), stride=64, step=7, bits=(4,))     # many chunks, few of them of blocks
+           + case((1, 1, 1), 5, 4, 24, 601, 0.3, (9, 16), stride=3)                # few, more of blocks
+           + case((1, 1, 2), 5, 4, 8, 6003, 0.05, (9, 16), stride=12, step=7)
+           + case((1, 1, 3), 5, 4, 4, 10005, 0.05, (8, 16), stride=12, step=7)
+           + case((1, 2, 1), 16, 65, 6, 601, 0.3, (2, 5), stride=4)                # four wavefronts
+           + case((1, 1, 1), 16, 65, 16, 601, 0.3, (6, 10), stride=4))
 CASES = RESIDUAL + ONE_SET
 
 
@@ -47,7 +48,11 @@ def options(c):
     return dict(max_granularity=2 if c["stride"] else 1, num_panels=c["panels"], delta_bits=c["bits"])
 
 
+def block_chunks(stats):
+    return sum(stats.units_by_g[1:]) / 4
+
+
 def chunks(stats):
     """what a wavefront takes at a time, of one image: 64 lane units, 4 units (the rule counts the last one of a panel and set in full, up
     to one more for each)"""
-    return stats.units_by_g[0] / 64 + sum(stats.units_by_g[1:]) / 4
+    return stats.units_by_g[0] / 64 + block_chunks(stats)

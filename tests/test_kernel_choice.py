@@ -25,6 +25,7 @@ for c in arg:
     B.ecspmv_run_batch(mats, [X + 2 * (k % 2) for k in range(c["count"])], [Y] * c["count"], 0)
     st = [A.ecspmv_stats() for A in mats]
     out.append(dict(kernel=kernel(), grid=fake.fake_launched(GRID), chunks=sum(C.chunks(s) for s in st) / sum(s.num_panels for s in st),
+                    per_wave=64 * sum(C.block_chunks(s) for s in st) / fake.fake_launched(GRID) / fake.fake_launched(THREADS),
                     sets=[int(any(s.units_by_g[g] for s in st)) for g in range(1, 5)]))
 print(json.dumps(out))
 """
@@ -36,6 +37,8 @@ def test_several_matrices(tmp_path, cases):
         tm, mode, k = c["kernel"]
         assert c["chunks"][0] <= got["chunks"] <= c["chunks"][1], (c, got)           # the case is what it says
         assert got["grid"] == c["panels"] * c["count"] and got["sets"] == [tm, 0, 0, 0], (c, got)
+        if tm:
+            assert (got["per_wave"] < 0.7) if mode == 2 else (got["per_wave"] > 0.76), (c, got)
         assert got["kernel"] == [tm, c["bits"], mode, k, 1, 2], (c, got)
 
 
