@@ -824,7 +824,8 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // 50 % 5.07 / 4.95, twelve 1024 x 1500 at 30 % 5.07 / 4.85, five 1001 x 2047 at 40 %, 8-bit 5.27 / 4.9, six 601 x 1701 at 30 %, 8-bit
     // 4.0 / 3.85, the four launches of a 2049 / 5506 layer 19.7 / 18.5.  What the branch costs where nothing is left: the four
     // launches of a 4096 / 11008 layer, 8-bit, 44.1 / 44.2, the same behind the header or with the load out of line.)
-    if (tid < (x_fast ? n % 8u : 0u)) xs[nvec * 8u + tid] = x[nvec * 8u + tid];
+    if constexpr (NB * VW % 16 != 0)        // (rows of whole pieces leave nothing)
+        if (tid < (x_fast ? n % 8u : 0u)) xs[nvec * 8u + tid] = x[nvec * 8u + tid];
     __builtin_amdgcn_sched_barrier(0);      // these loads do not wait for the header: keep them ahead of those that do
 #pragma unroll
     for (int w = 0; w < (int)(ECS_PANEL_HEADER / 4); ++w) {
