@@ -121,7 +121,8 @@ int ecspmv_build_dense(const uint16_t *W, int64_t m, int64_t n, int64_t ld,
 
 /* The same from CSR (the form pruned weights usually come in).
  * rowptr: host, m+1 entries, rowptr[0] = 0, non-decreasing; col: host, strictly increasing
- * within a row, in [0, n); val: host FP16 bits (entries equal to +-0 are dropped). */
+ * within a row, in [0, n); val: host FP16 bits (entries equal to +-0 are dropped).  Beside the image a build takes memory
+ * by the entries (some 25 bytes each) and the rows, not by m * n, but for the panels its threads work on. */
 int ecspmv_build_csr(const int64_t *rowptr, const int32_t *col, const uint16_t *val,
                      int64_t m, int64_t n, const ecspmv_build_opts *opts, ecspmv_matrix **out);
 
