@@ -52,11 +52,11 @@ __device__ __forceinline__ int dpp_i(int old, int src)
 {
     return __builtin_amdgcn_update_dpp(old, src, CTRL, ROW_MASK, 0xF, false);
 }
-template <int CTRL, int ROW_MASK = 0xF>
+template <int CTRL, int ROW_MASK = 0xF, int BANK_MASK = 0xF>
 __device__ __forceinline__ float dpp_f(float old, float src)
 {
     return __int_as_float(
-        __builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(src), CTRL, ROW_MASK, 0xF, false));
+        __builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(src), CTRL, ROW_MASK, BANK_MASK, false));
 }
 
 #ifndef ECS_D4
@@ -75,6 +75,7 @@ __device__ __forceinline__ float dpp_f(float old, float src)
 constexpr int D4 = ECS_D4, D2 = ECS_D2, DR = ECS_DR, DR0B = ECS_DR0B;
 
 constexpr int DPP_ROW_SHR1 = 0x111, DPP_ROW_SHR2 = 0x112, DPP_ROW_SHR4 = 0x114, DPP_ROW_SHR8 = 0x118;
+constexpr int DPP_ROW_SHL4 = 0x104, DPP_ROW_SHL8 = 0x108;
 constexpr int DPP_ROW_BCAST15 = 0x142, DPP_ROW_BCAST31 = 0x143;
 constexpr int DPP_QUAD_1032 = 0xB1, DPP_QUAD_2301 = 0x4E, DPP_ROW_HALF_MIRROR = 0x141, DPP_ROW_MIRROR = 0x140;
 
@@ -105,6 +106,39 @@ __device__ __forceinline__ float row16_allreduce(float a)
     a += dpp_f<DPP_ROW_HALF_MIRROR>(0.0f, a);
     a += dpp_f<DPP_ROW_MIRROR>(0.0f, a);
     return a;
+}
+
+// Sums of N values over the 16 lanes of a DPP row, the k-th in lane k (lanes from N on hold anything).  The same additions as
+// row16_allreduce makes for each, but from step to step a lane keeps half of the values it has: 6 instructions in the place of 9
+// for two values, 11 of 19 for four, 23 of 39 for eight.  Cross-lane additions take 4.3 cycles of a SIMD, and with several
+// right-hand sides the vector instructions are what a launch waits for: us by 4 N additions / by these, 4096 x 4096 at 50 %,
+// 8-bit (8-, 4- and 2-grained sets), eight 11.3 / 10.1, two 6.8 / 6.5; 2048 x 2048, four 4.80 / 4.51; 11008 x 4096 at 40 %, 8-bit,
+// four 12.0 / 11.5; without block sets, where only rows of y are added up, 13824 x 5120 at 30 %, eight 17.8 / 17.5.  One vector
+// gains 0-1 % (4096 x 4096 at 50 %, 4-bit 5.82 / 5.73).
+template <int N>
+__device__ __forceinline__ float row16_sums(const float (&a)[N], uint32_t j)
+{
+    static_assert(N == 2 || N == 4 || N == 8, "a power of two, at most half of the lanes");
+    auto pick = [](bool up, float lo, float hi) { return up ? hi : lo; };
+    float h[N / 2];
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k)
+        h[k] = pick(j & 1u, a[2 * k] + dpp_f<DPP_QUAD_1032>(0.0f, a[2 * k]), a[2 * k + 1] + dpp_f<DPP_QUAD_1032>(0.0f, a[2 * k + 1]));
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) h[k] += dpp_f<DPP_QUAD_2301>(0.0f, h[k]);
+    if constexpr (N > 2)
+#pragma unroll
+        for (int k = 0; k < N / 4; ++k) h[k] = pick(j & 2u, h[2 * k], h[2 * k + 1]);
+    // the first quad takes its sums of the second one, the first half those of the second; with eight values the second quad keeps the
+    // upper four instead
+    float t = h[0];
+    if constexpr (N == 8) {
+        const float other = dpp_f<DPP_ROW_SHL4, 0xF, 0x5>(0.0f, h[0]);
+        t = pick(j & 4u, h[0], h[1]) + dpp_f<DPP_ROW_SHR4, 0xF, 0xA>(other, h[1]);
+    } else {
+        t += dpp_f<DPP_ROW_SHL4>(0.0f, t);
+    }
+    return t + dpp_f<DPP_ROW_SHL8>(0.0f, t);
 }
 
 __device__ __forceinline__ float half_bits_to_float(uint32_t h)
@@ -315,12 +349,20 @@ __device__ __forceinline__ void compute_unit(const Ctx &c, const uint16_t *utab,
         typename P::vec t;
 #pragma unroll
         for (int k = 0; k < P::G; ++k) {
+            float rows[G];
 #pragma unroll
-            for (int q = 0; q < G; ++q) acc[q][k] = row16_allreduce(acc[q][k]);
-            float out = acc[0][k];
+            for (int q = 0; q < G; ++q) rows[q] = acc[q][k];
+            if constexpr (G < 16) {
+                t[k] = row16_sums<G>(rows, j);
+            } else {                                // (the halves of 16 values take 3 registers too many, with 16-bit columns)
+                float out = row16_allreduce(rows[0]);
 #pragma unroll
-            for (int q = 1; q < G; ++q) out = (j == (uint32_t)q) ? acc[q][k] : out;
-            t[k] = out;
+                for (int q = 1; q < G; ++q) {
+                    const float sum = row16_allreduce(rows[q]);
+                    out = j == (uint32_t)q ? sum : out;
+                }
+                t[k] = out;
+            }
         }
         if (active && j < (uint32_t)G) reinterpret_cast<typename P::vec *>(c.slots)[ue[1 + j] + p * c.pstride] = t;
     }
@@ -972,14 +1014,9 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
             }
         }
     } else {
-        // every lane has every total: lane k stores the k-th
+        // lane k stores the k-th total
         auto store = [&](uint32_t r, const float (&sum)[NB]) {
-            float out = 0.0f;
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const float t = row16_allreduce(sum[k]);
-                out = j == (uint32_t)k ? t : out;
-            }
+            const float out = row16_sums<NB>(sum, j);
             if (j < (uint32_t)NB) {
                 if constexpr (VW == 2)
                     y[(size_t)rowidx[r] * ld + j] = __half_as_ushort(__float2half_rn(out));
