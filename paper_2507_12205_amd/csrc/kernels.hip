@@ -699,7 +699,7 @@ struct NoTable {};
 // lines are in launch_tm), 3 = one SpMV with four or eight right-hand sides whose residual chunks are taken in
 // phases (a mode of its own: the loop over phases costs launches that need one phase only 2-9 %, two vectors on
 // 16384 x 1024, 4-bit 6.5 us without it and 7.1 with it, 768 x 768 with four 3.56 and 3.76);
-// K: 16-byte pieces of [tables | x] each thread brings to LDS before the generic loop takes the rest;
+// K: 16-byte pieces of [tables | x] each thread brings to LDS before the rest follows; 5: four, and the rest directly;
 // NB: right-hand sides handled at once (x holds n rows of NB values, y m rows of NB values);
 // VW: bytes per value of W, x and y (2 = FP16, 4 = FP32)
 template <int TM, int DB, int MODE, int K, int NB, int VW>
@@ -767,8 +767,9 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
 
     extern __shared__ uint4 lds4[];
     uint8_t *lds = reinterpret_cast<uint8_t *>(lds4);
-    uint16_t *xs = reinterpret_cast<uint16_t *>(lds);
-    uint8_t *meta = lds + x_bytes;
+    constexpr bool DIRECT = K == 5 || (K == 4 && NB > 1);           // what four pieces per thread leave goes straight to LDS (below)
+    uint16_t *xs = reinterpret_cast<uint16_t *>(DIRECT ? lds + meta_stride : lds);
+    uint8_t *meta = DIRECT ? lds : lds + x_bytes;
     float *slots = reinterpret_cast<float *>(lds + x_bytes + meta_stride);
     // phases: chunks a wavefront takes per phase (the count of matrices is 1), and the 16 lanes' sums of the row that runs
     // on into the next phase, kept for two phases in turn
@@ -807,7 +808,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // buffers per set: deeper where chunks are small and frequent, shallower where registers run out.  Four right-hand sides
     // with 2- and 4-grained sets are kept at 64 VGPRs, so that two workgroups of 1024 threads share a compute unit where LDS
     // allows (20480 x 1024 at 50 %, 8-bit, in 512 panels: 9.1 us, with 71 VGPRs 10.8; in 256 panels 4096 x 11008 at 40 % 13.8
-    // against 14.3): one buffer for the 2-grained set, two pieces at a time in the staging loop, and the residual set
+    // against 14.3): one buffer for the 2-grained set, and the residual set
     // requested after the first 4-grained chunk.
     constexpr bool wide = (TM & 12) != 0, tight = NB == 4 && VW == 2 && TM == 3;
     constexpr bool straight = !BATCH;
@@ -853,6 +854,20 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
         const uint32_t idx = piece_index(k);
         return idx < nmeta ? p4 + idx : xsrc + (idx - nmeta);
     };
+    // What is left beyond four pieces per thread goes from memory straight to LDS, where tables and x then lie in the order of the list,
+    // a wavefront's 64 pieces side by side.  It needs no registers, so that all of it travels at once, in one trip to the L2 or beyond
+    // with everything else, and it is requested first: loads return in the order in which they were requested, so that it is there when
+    // this wavefront has its header and its four pieces.  In a loop of one to four loads behind those four it took a trip for each
+    // round: us there / here, four right-hand sides 5120 x 13824 at 30 % 13.5 / 13.1 (cold 14.1 / 13.5), 2048 x 11008 at 40 %, 8-bit 11.1 /
+    // 10.9, two, 4096 x 16000 at 20 % 8.11 / 7.91, eight, 768 x 6144 at 50 % 11.68 / 11.54; FP32, one vector, 2048 x 20000 at 20 %, 8-bit
+    // 12.7 / 11.9.
+    if constexpr (DIRECT)
+        for (uint32_t at = 64u * c.wave + 4u * nt; at < ntot; at += nt) {
+            const uint32_t idx = at + c.lane;
+            if (idx < ntot)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(idx < nmeta ? p4 + idx : xsrc + (idx - nmeta)),
+                                                 (__attribute__((address_space(3))) void *)(lds + 16u * at), 16, 0, 0);
+        }
     ECS_STAMP(c, 22);           // just before the header request
     const uint4 hv = reinterpret_cast<const uint4 *>(panel)[c.lane & 7u];
     ECS_STAMP(c, 23);           // header requested
@@ -910,19 +925,20 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // tables and x into LDS
     // (no branches here either: with a store under a branch the compiler moves the load down to it and waits for
     // it there)
-    auto put = [&](uint32_t idx, const uint4 &t) { *(idx < nmeta ? meta4 + idx : lds4 + (idx - nmeta)) = t; };
+    auto put = [&](uint32_t idx, const uint4 &t) { *(DIRECT ? lds4 + idx : idx < nmeta ? meta4 + idx : lds4 + (idx - nmeta)) = t; };
     put(piece_index(0), s0);
     if constexpr (K > 1) put(piece_index(1), s1);
     if constexpr (K > 2) put(piece_index(2), s2);
     if constexpr (K > 3) put(piece_index(3), s3);
-    static_assert(K <= 4, "at most four pieces per thread are brought here");
-    // With K < 4 the list is covered (the launch counts its pieces); what is left with K = 4 comes in rounds of U loads per
-    // thread that travel together (a round is a trip to the L2 or beyond).  One vector: two, as far as the registers of the
+    static_assert(K <= 5, "at most four pieces per thread are brought here");
+    // With K < 4 the list is covered (the launch counts its pieces), and with FP32 values and K = 4; what is left of it with K = 4, FP16
+    // and one vector comes in rounds of U loads per
+    // thread that travel together (a round is a trip to the L2 or beyond): two, as far as the registers of the
     // launches with several matrices go: three 5120 x 20480 in one launch 32.2 -> 30.2 us, two 19.9 -> 19.6; four: 29.8, but
     // FP32 sixteen 1000 x 10000 16.5 -> 18.7.  A launch of one matrix has more threads and hardly ever gets here: one at
     // a time, the code around it is then 1 % faster (5120 x 20480 10.90 -> 10.79).
-    if constexpr (K == 4) {
-        constexpr uint32_t U = NB == 1 ? (LONE ? 1 : 2) : NB == 2 || NB * VW >= 32 ? 1 : tight ? 2 : 4;
+    if constexpr (K == 4 && NB == 1 && VW == 2) {
+        constexpr uint32_t U = LONE ? 1 : 2;
         for (uint32_t idx = tid + (uint32_t)K * nt; idx < ntot; idx += U * nt) {
             uint4 t[U];
 #pragma unroll
@@ -934,6 +950,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
             for (uint32_t u = 0; u < U; ++u) put(min(idx + u * nt, ntot - 1u), t[u]);
         }
     }
+    if constexpr (DIRECT && NB > 1) __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): nothing is left on its way
     // all of x if it is not 16-byte aligned or its rows are longer than the NB values this launch takes
     if (NB > 1 && NB < 8 && ld != NB) {
         // one load of NB values per row of X where the alignment allows it (ld counts values of VW bytes)
@@ -1291,6 +1308,8 @@ static int launch_b(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
     // gain nothing (4096 x 11008 15.65 / 15.77, 2048 x 11008 10.63 / 10.73).
     if constexpr (VW == 2)
         if (per_thread <= 3) return launch_k<TM, DB, BATCH, 3, 1>(batch, threads, lds_bytes, stream);
+    if constexpr (VW == 4)
+        if (per_thread > 4) return launch_k<TM, DB, BATCH, 5, 1, VW>(batch, threads, lds_bytes, stream);
     return launch_k<TM, DB, BATCH, 4, 1, VW>(batch, threads, lds_bytes, stream);
 }
 

@@ -106,3 +106,12 @@ def test_phases(tmp_path):
     assert phases["kernel"] == [0, 4, 3, 4, 8, 2] and phases["grid"] == 1
     assert split["kernel"][2] in (0, 3) and split["kernel"][4:] == [4, 2] and split["grid"] == 2
     assert all(g["lds"] <= 160 * 1024 for g in (one, phases, split))
+
+
+def test_rest_directly_fp32(tmp_path):
+    """FP32, one vector: up to four pieces per thread, and more"""
+    threads = 128
+    cases = [dict(nb=1, fp32=True, bits=bits, threads=threads, rows=8, density=0.1, pieces=4 * threads) for bits in (4, 8)]
+    for c, got in zip(cases, standin.run(tmp_path, PIECES, cases)):
+        assert got["at"][0] <= c["pieces"] < got["at"][1], (c, got)
+        assert got["below"] == [0, c["bits"], 0, 4, 1, 4] and got["above"] == [0, c["bits"], 0, 5, 1, 4], (c, got)
