@@ -690,6 +690,7 @@ struct ResidualSet {
 // What a launch of a single SpMV carries in the place of the table of matrices: the host is what a sequence of small
 // launches waits for, and it need not write 784 bytes that no one reads.
 struct NoTable {};
+constexpr bool alone(int mode) { return mode == 0 || mode >= 3; }
 
 // TM: bit t set = the image holds units of granularity 2 << t somewhere (the residual set is always handled);
 // DB: width of the delta indices in bits; MODE: 0 = a launch that carries one SpMV (nothing of the batch table is
@@ -698,7 +699,8 @@ struct NoTable {};
 // (residual-only images: two buffers) or few block units (one block set: everything requested before the first barrier; the
 // lines are in launch_tm), 3 = one SpMV with four or eight right-hand sides whose residual chunks are taken in
 // phases (a mode of its own: the loop over phases costs launches that need one phase only 2-9 %, two vectors on
-// 16384 x 1024, 4-bit 6.5 us without it and 7.1 with it, 768 x 768 with four 3.56 and 3.76);
+// 16384 x 1024, 4-bit 6.5 us without it and 7.1 with it, 768 x 768 with four 3.56 and 3.76), 4 = one SpMV whose x is brought before
+// the first chunks are requested (launch_b);
 // K: 16-byte pieces of [tables | x] each thread brings to LDS before the rest follows; 5: four, and the rest directly;
 // NB: right-hand sides handled at once (x holds n rows of NB values, y m rows of NB values);
 // VW: bytes per value of W, x and y (2 = FP16, 4 = FP32)
@@ -708,7 +710,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
                                                       const uint32_t panel_stride0, const uint32_t meta_stride0,
                                                       const uint32_t x_bytes0, const uint32_t block_end0,
                                                       const uint32_t row_stride0, const uint64_t trace_words,
-                                                      const std::conditional_t<MODE == 0 || MODE == 3, NoTable, ecs::EcsBatch> batch)
+                                                      const std::conditional_t<alone(MODE), NoTable, ecs::EcsBatch> batch)
 {
 #ifdef ECS_TRACE
     const uint64_t t_start = __builtin_amdgcn_s_memtime(), t_start_real = __builtin_amdgcn_s_memrealtime();
@@ -718,7 +720,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // plain values the hardware can hand over in registers; the table behind them is read only by launches that
     // carry several SpMVs: one 16-byte vector load per lane fetches all of it (scalar loads by every wavefront of a
     // workgroup are served one wavefront after the other), and the item is then read out of the lanes.
-    constexpr bool BATCH = MODE == 2, LONE = MODE == 0 || MODE == 3, PHASES = MODE == 3;
+    constexpr bool BATCH = MODE == 2, LONE = alone(MODE), PHASES = MODE == 3, X_FIRST = NB > 1 || MODE == 4;
     ecs::EcsBatchItem it;
     it.image = image0, it.x = x0, it.y = y0, it.n = n0, it.panel_stride = panel_stride0, it.meta_stride = meta_stride0;
     it.x_bytes = x_bytes0, it.block_end = block_end0, it.row_stride = 0;
@@ -914,7 +916,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
         if constexpr (!residual_late) rs.prologue(c, hdr, dealt);
     };
     ECS_STAMP(c, 1);            // panel header here
-    if constexpr (NB == 1) request_first();
+    if constexpr (!X_FIRST) request_first();
     ECS_STAMP(c, 2);            // first chunks of every set requested
 
 #ifdef ECS_TRACE
@@ -977,7 +979,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     } else if (!x_fast) {
         for (uint32_t i = tid; i < n; i += nt) xs[i] = x[i];
     }
-    if constexpr (NB > 1) request_first();
+    if constexpr (X_FIRST) request_first();
     ECS_STAMP(c, 3);            // this wavefront's pieces of the tables and x written to LDS
     __syncthreads();
     ECS_STAMP(c, 4);            // first barrier passed
@@ -1238,7 +1240,7 @@ static int kernel_handle(void *stream, hipFunction_t *f)
 template <int TM, int DB, int MODE, int K, int NB, int VW = 2>
 static int launch_m(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, void *stream)
 {
-    typedef std::conditional_t<MODE == 0 || MODE == 3, NoTable, EcsBatch> Table;
+    typedef std::conditional_t<alone(MODE), NoTable, EcsBatch> Table;
     static thread_local uint32_t attr_set_for = 0;
     if (lds_bytes > 65536 && lds_bytes > attr_set_for) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(ecspmv_kernel<TM, DB, MODE, K, NB, VW>),
@@ -1287,7 +1289,7 @@ static int launch_k(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
 }
 
 template <int TM, int DB, bool BATCH, int VW = 2>
-static int launch_b(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, void *stream)
+static int launch_b(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, uint64_t chunks, void *stream)
 {
     // staging pieces per thread: the largest [tables | x] list of the batch over the workgroup size
     uint32_t most = 1;
@@ -1298,6 +1300,22 @@ static int launch_b(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
         most = pieces > most ? pieces : most;
     }
     const uint32_t per_thread = (most + threads - 1) / threads;
+    // One vector alone, FP16, residual set only: the first chunks are requested once this wavefront's part of x is in LDS, as with several
+    // vectors, where a panel has more than 30 chunks and x is three pieces per thread or more, or two with 8-bit deltas or on a chip that
+    // is not full.  us with the chunks / x first: three pieces, 5120 x 20480 at 20 % 11.2 / 11.0, 2048 x 20480 at 30 % 10.4 / 10.0, 1459 x
+    // 16576 at 10 % (33 chunks) 5.72 / 5.53, 8-bit 1422 x 15104 at 20 % 7.0 / 6.4; two, 8-bit 11756 x 7936 at 20 % 11.1 / 10.8, 837 x 13696 at
+    // 30 % 7.9 / 7.4, 4-bit 1310 x 10688 at 30 % (81 panels) 6.75 / 6.40, 1086 x 11289 at 20 % (67) 5.52 / 5.35; but with 256 panels 5120 x
+    // 13824 at 30 % 10.7 / 10.6 over and over and 0.2 us slower among the seven products of a layer, 8192 x 8192 10.12 / 10.15; 6067 x 9002
+    // at 10 % (26 chunks) 5.33 / 5.34, 909 x 11171 (22) 4.08 / 4.19, 2305 x 6528 (13) 3.86 / 4.06; one piece 5120 x 5120 5.79 / 5.95.  With
+    // block sets some gain and some lose (1090 x 8000 at 40 % 6.43 / 6.27, 3256 x 9155 at 50 % 9.14 / 9.27), FP32 values lose (4096 x 8192 at
+    // 30 % 9.25 / 9.59), and so do several matrices (16 x 1024 x 4096 10.2 / 10.5).
+    if constexpr (TM == 0 && VW == 2 && !BATCH)
+        if (const uint32_t panels = batch.item[0].block_end; batch.count == 1 && chunks > 30u * (uint64_t)panels &&
+            (per_thread > 2 || (per_thread == 2 && (DB == 8 || panels < 256u)))) {
+            if (per_thread == 2) return launch_m<TM, DB, 4, 2, 1, VW>(batch, threads, lds_bytes, stream);
+            if (per_thread == 3) return launch_m<TM, DB, 4, 3, 1, VW>(batch, threads, lds_bytes, stream);
+            return launch_m<TM, DB, 4, 4, 1, VW>(batch, threads, lds_bytes, stream);
+        }
     if constexpr (VW == 2)
         if (per_thread <= 1) return launch_k<TM, DB, BATCH, 1, 1>(batch, threads, lds_bytes, stream);
     if (per_thread <= 2) return launch_k<TM, DB, BATCH, 2, 1, VW>(batch, threads, lds_bytes, stream);
@@ -1320,8 +1338,8 @@ static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes
     // FP32 values: lone-launch buffer depths
     if (value_bits == 32) {
         if (delta_bits == 16) return (int)hipErrorInvalidValue;
-        return delta_bits == 4 ? launch_b<TM, 4, false, 4>(batch, threads, lds_bytes, stream)
-                               : launch_b<TM, 8, false, 4>(batch, threads, lds_bytes, stream);
+        return delta_bits == 4 ? launch_b<TM, 4, false, 4>(batch, threads, lds_bytes, chunks, stream)
+                               : launch_b<TM, 8, false, 4>(batch, threads, lds_bytes, chunks, stream);
     }
     // index compression switched off (absolute 16-bit columns): the ablation point, one variant per set mask
     if (delta_bits == 16) return launch_k<TM, 16, false, 4, 1>(batch, threads, lds_bytes, stream);
@@ -1342,10 +1360,10 @@ static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes
     const uint64_t grid = batch.item[batch.count - 1].block_end;
     const bool second = TM == 0 ? grid > 512u && chunks > 45u * grid : TM == 1 && 4u * block_chunks <= 3u * grid * (threads / 64u);
     if (batch.count > 1 && second)
-        return delta_bits == 4 ? launch_b<TM, 4, TM <= 1>(batch, threads, lds_bytes, stream)
-                               : launch_b<TM, 8, TM <= 1>(batch, threads, lds_bytes, stream);
-    return delta_bits == 4 ? launch_b<TM, 4, false>(batch, threads, lds_bytes, stream)
-                           : launch_b<TM, 8, false>(batch, threads, lds_bytes, stream);
+        return delta_bits == 4 ? launch_b<TM, 4, TM <= 1>(batch, threads, lds_bytes, chunks, stream)
+                               : launch_b<TM, 8, TM <= 1>(batch, threads, lds_bytes, chunks, stream);
+    return delta_bits == 4 ? launch_b<TM, 4, false>(batch, threads, lds_bytes, chunks, stream)
+                           : launch_b<TM, 8, false>(batch, threads, lds_bytes, chunks, stream);
 }
 
 // several right-hand sides: one matrix per launch, images with 8-grained sets at most; the staging variant as with one vector

@@ -115,3 +115,32 @@ def test_rest_directly_fp32(tmp_path):
     for c, got in zip(cases, standin.run(tmp_path, PIECES, cases)):
         assert got["at"][0] <= c["pieces"] < got["at"][1], (c, got)
         assert got["below"] == [0, c["bits"], 0, 4, 1, 4] and got["above"] == [0, c["bits"], 0, 5, 1, 4], (c, got)
+
+
+X_FIRST = HEAD + r"""
+out = []
+for c in arg:
+    rng = np.random.default_rng(1)
+    W = np.where(rng.random((c["rows"], c["n"])) < c["density"], np.float16(0.5), np.float16(0)).astype(np.float32 if c["fp32"] else np.float16)
+    if c["stride"]: W[:, ::c["stride"]] = 0.5
+    A = upload(W, max_granularity=2 if c["stride"] else 1, delta_bits=c["bits"], num_panels=c["panels"])
+    B.ecspmv_run_batch([A] * c["count"], [X] * c["count"], [Y] * c["count"], 0)
+    st = A.ecspmv_stats()
+    out.append(dict(kernel=kernel(), chunks=st.units_by_g[0] / 64 / c["panels"]))
+print(json.dumps(out))
+"""
+
+
+def test_x_first(tmp_path):
+    """residual set only, alone, FP16, more than 30 chunks a panel, and three pieces per thread or more, or two with 8-bit deltas or
+    fewer than 256 panels; and each of these not so"""
+    base = dict(rows=40, n=9000, density=0.2, bits=4, panels=2, count=1, fp32=False, stride=0)
+    full = dict(base, rows=18 * 256, panels=256, density=0.21)
+    cases = [base, dict(base, bits=8), dict(base, n=17000, density=0.11), dict(base, n=33000, density=0.06), dict(full, bits=8),
+             dict(full, rows=18 * 255, panels=255), dict(full, n=17000, density=0.11),
+             full, dict(base, density=0.15), dict(base, n=4000, density=0.5), dict(base, count=2), dict(base, fp32=True),
+             dict(base, stride=10)]
+    got = standin.run(tmp_path, X_FIRST, cases)
+    assert [g["kernel"][2:4] for g in got] == [[4, 2], [4, 2], [4, 3], [4, 4], [4, 2], [4, 2], [4, 3], [0, 2], [0, 2], [0, 1], [1, 3], [0, 4],
+                                               [0, 2]], got
+    assert all(31 < g["chunks"] < 70 for g in got[:8]) and 20 < got[8]["chunks"] < 30, got
