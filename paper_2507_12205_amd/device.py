@@ -27,7 +27,7 @@ def run(mat: B.Matrix, x: torch.Tensor, y: torch.Tensor, stream=None) -> torch.T
     """y = W x on the given (or current) stream; x, y are CUDA tensors of length n, m: FP16, or FP32 for a matrix
     built from FP32 values."""
     want = torch.float32 if mat.value_bits == 32 else torch.float16
-    assert x.dtype == want and y.dtype == want and x.is_cuda and y.is_cuda
+    assert x.dtype is want and y.dtype is want and x.is_cuda and y.is_cuda
     assert x.is_contiguous() and y.is_contiguous()
     mat.ecspmv_run(x.data_ptr(), y.data_ptr(), _stream_handle(stream))
     return y
@@ -37,7 +37,7 @@ def run_multi(mat: B.Matrix, X: torch.Tensor, Y: torch.Tensor, stream=None) -> t
     """Y = W X for X of shape (n, nb), Y of shape (m, nb), row-major, nb in {1, 2, 4, 8}; FP16, or FP32 for a matrix
     built from FP32 values."""
     want = torch.float32 if mat.value_bits == 32 else torch.float16
-    assert X.dtype == want and Y.dtype == want and X.is_cuda and Y.is_cuda
+    assert X.dtype is want and Y.dtype is want and X.is_cuda and Y.is_cuda
     assert X.dim() == 2 and Y.dim() == 2 and X.shape[1] == Y.shape[1] and X.is_contiguous() and Y.is_contiguous()
     mat.ecspmv_run_multi(X.data_ptr(), Y.data_ptr(), int(X.shape[1]), _stream_handle(stream))
     return Y
