@@ -934,11 +934,11 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     if constexpr (K > 3) put(piece_index(3), s3);
     static_assert(K <= 5, "at most four pieces per thread are brought here");
     // With K < 4 the list is covered (the launch counts its pieces), and with FP32 values and K = 4; what is left of it with K = 4, FP16
-    // and one vector comes in rounds of U loads per
-    // thread that travel together (a round is a trip to the L2 or beyond): two, as far as the registers of the
-    // launches with several matrices go: three 5120 x 20480 in one launch 32.2 -> 30.2 us, two 19.9 -> 19.6; four: 29.8, but
-    // FP32 sixteen 1000 x 10000 16.5 -> 18.7.  A launch of one matrix has more threads and hardly ever gets here: one at
-    // a time, the code around it is then 1 % faster (5120 x 20480 10.90 -> 10.79).
+    // and one vector comes in rounds of U loads per thread that travel together (a round is a trip to the L2 or beyond): two, as far
+    // as the registers of the launches with several matrices go: three 5120 x 20480 in one launch 32.2 -> 30.2 us, two 19.9 -> 19.6;
+    // four: 29.8, but FP32 sixteen 1000 x 10000 16.5 -> 18.7.  (Directly to LDS: 1-5 % faster, but the launches whose four pieces bring
+    // all of x 1 % slower, three 2048 x 12000 9.3 / 9.4.)  A launch of one matrix has more threads and hardly ever gets here: one at a
+    // time, the code around it is then 1 % faster (5120 x 20480 10.90 -> 10.79).
     if constexpr (K == 4 && NB == 1 && VW == 2) {
         constexpr uint32_t U = LONE ? 1 : 2;
         for (uint32_t idx = tid + (uint32_t)K * nt; idx < ntot; idx += U * nt) {
@@ -1368,7 +1368,7 @@ static int launch_tm(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes
 
 // several right-hand sides: one matrix per launch, images with 8-grained sets at most; the staging variant as with one vector
 // (us, two, 5120 x 5120 at 30 %, two pieces per thread: by the variant for four 6.38, for two 5.85;
-// four, 16384 x 1024 at 30 %, one piece 5.55 / 4.80, 5120 x 5120 at 30 %, 8-bit, three 7.35 / 6.90; six or eight
+// four, 16384 x 1024 at 30 %, one piece 5.55 / 4.80, 5120 x 5120 at 30 %, 8-bit, three 7.35 / 6.90; six or eight through registers
 // at once are slower than four and a loop: FP32 4096 x 4096, four, 6.81 / 7.55 / 7.48).  Phases are for an X that takes them all.
 template <int TM, int DB, int NB, int VW>
 static int launch_nk(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes, void *stream)
