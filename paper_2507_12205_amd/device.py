@@ -11,7 +11,10 @@ def _stream_handle(stream=None) -> int:
     building torch's stream object takes 2.8 us, as long as the launch itself)."""
     if stream is not None:
         return int(stream.cuda_stream)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_device())
+
+
+_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
 
 def upload(mat: B.Matrix, device="cuda:0", stream=None) -> torch.Tensor:
@@ -29,7 +32,7 @@ def run(mat: B.Matrix, x: torch.Tensor, y: torch.Tensor, stream=None) -> torch.T
     want = torch.float32 if mat.value_bits == 32 else torch.float16
     assert x.dtype is want and y.dtype is want and x.is_cuda and y.is_cuda
     assert x.is_contiguous() and y.is_contiguous()
-    mat.ecspmv_run(x.data_ptr(), y.data_ptr(), _stream_handle(stream))
+    mat.ecspmv_run(x.data_ptr(), y.data_ptr(), _raw_stream(_device()) if stream is None else _stream_handle(stream))
     return y
 
 
@@ -39,7 +42,7 @@ def run_multi(mat: B.Matrix, X: torch.Tensor, Y: torch.Tensor, stream=None) -> t
     want = torch.float32 if mat.value_bits == 32 else torch.float16
     assert X.dtype is want and Y.dtype is want and X.is_cuda and Y.is_cuda
     assert X.dim() == 2 and Y.dim() == 2 and X.shape[1] == Y.shape[1] and X.is_contiguous() and Y.is_contiguous()
-    mat.ecspmv_run_multi(X.data_ptr(), Y.data_ptr(), int(X.shape[1]), _stream_handle(stream))
+    mat.ecspmv_run_multi(X.data_ptr(), Y.data_ptr(), X.shape[1], _raw_stream(_device()) if stream is None else _stream_handle(stream))
     return Y
 
 
