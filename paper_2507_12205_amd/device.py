@@ -2,19 +2,18 @@
 from __future__ import annotations
 
 import torch
+from torch import _C
 
 from . import binding as B
 
 
 def _stream_handle(stream=None) -> int:
     """The HIP stream to launch on: the given one, or the current one of the current device (asked for as a plain handle:
-    building torch's stream object takes 2.8 us, as long as the launch itself)."""
+    building torch's stream object takes 2.8 us, as long as the launch itself).  Only a call without a stream needs these two
+    private functions of torch."""
     if stream is not None:
         return int(stream.cuda_stream)
-    return _raw_stream(_device())
-
-
-_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    return _C._cuda_getCurrentRawStream(_C._cuda_getDevice())
 
 
 def upload(mat: B.Matrix, device="cuda:0", stream=None) -> torch.Tensor:
@@ -32,7 +31,7 @@ def run(mat: B.Matrix, x: torch.Tensor, y: torch.Tensor, stream=None) -> torch.T
     want = torch.float32 if mat.value_bits == 32 else torch.float16
     assert x.dtype is want and y.dtype is want and x.is_cuda and y.is_cuda
     assert x.is_contiguous() and y.is_contiguous()
-    mat.ecspmv_run(x.data_ptr(), y.data_ptr(), _raw_stream(_device()) if stream is None else _stream_handle(stream))
+    mat.ecspmv_run(x.data_ptr(), y.data_ptr(), _C._cuda_getCurrentRawStream(_C._cuda_getDevice()) if stream is None else _stream_handle(stream))
     return y
 
 
@@ -42,7 +41,8 @@ def run_multi(mat: B.Matrix, X: torch.Tensor, Y: torch.Tensor, stream=None) -> t
     want = torch.float32 if mat.value_bits == 32 else torch.float16
     assert X.dtype is want and Y.dtype is want and X.is_cuda and Y.is_cuda
     assert X.dim() == 2 and Y.dim() == 2 and X.shape[1] == Y.shape[1] and X.is_contiguous() and Y.is_contiguous()
-    mat.ecspmv_run_multi(X.data_ptr(), Y.data_ptr(), X.shape[1], _raw_stream(_device()) if stream is None else _stream_handle(stream))
+    mat.ecspmv_run_multi(X.data_ptr(), Y.data_ptr(), X.shape[1],
+                         _C._cuda_getCurrentRawStream(_C._cuda_getDevice()) if stream is None else _stream_handle(stream))
     return Y
 
 
