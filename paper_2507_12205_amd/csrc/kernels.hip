@@ -858,8 +858,8 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     };
     // What is left beyond four pieces per thread goes from memory straight to LDS, where tables and x then lie in the order of the list,
     // a wavefront's 64 pieces side by side.  It needs no registers, so that all of it travels at once, in one trip to the L2 or beyond
-    // with everything else, and it is requested first: loads return in the order in which they were requested, so that it is there when
-    // this wavefront has its header and its four pieces.  In a loop of one to four loads behind those four it took a trip for each
+    // with everything else, and it is requested first: loads return in the order in which they were requested, so that it is there about
+    // when this wavefront has its four pieces (what makes sure of it are the two waits below).  In a loop of one to four loads behind those four it took a trip for each
     // round: us there / here, four right-hand sides 5120 x 13824 at 30 % 13.5 / 13.1 (cold 14.1 / 13.5), 2048 x 11008 at 40 %, 8-bit 11.1 /
     // 10.9, two, 4096 x 16000 at 20 % 8.11 / 7.91, eight, 768 x 6144 at 50 % 11.68 / 11.54; FP32, one vector, 2048 x 20000 at 20 %, 8-bit
     // 12.7 / 11.9.
@@ -885,6 +885,10 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     // launches of a 4096 / 11008 layer, 8-bit, 44.1 / 44.2, the same behind the header or with the load out of line.)
     if constexpr (NB * VW % 16 != 0)        // (rows of whole pieces leave nothing)
         if (tid < (x_fast ? n % 8u : 0u)) xs[nvec * 8u + tid] = x[nvec * 8u + tid];
+    // What goes straight to LDS has no register that a use would wait for, and the barrier waits for no load: before it the source
+    // does, with one vector here (the compiler, which takes any store to LDS for one into the same bytes, waits here by itself, so the
+    // first chunks come behind all of x) and with several where this wavefront's pieces are in LDS.
+    if constexpr (DIRECT && NB == 1) __builtin_amdgcn_s_waitcnt(0x0F70);           // vmcnt(0)
     __builtin_amdgcn_sched_barrier(0);      // these loads do not wait for the header: keep them ahead of those that do
 #pragma unroll
     for (int w = 0; w < (int)(ECS_PANEL_HEADER / 4); ++w) {
@@ -898,7 +902,8 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     }
 
     // As soon as the header is here, the first chunks of every set are requested (one per register buffer), before
-    // anything is computed and before the tables and x have even reached LDS.  With several right-hand sides only once this
+    // anything is computed and before the tables and x have even reached LDS (K = 5: once all of x is here, see the wait above).  With
+    // several right-hand sides only once this
     // wavefront's part of X is in LDS: loads return in the order they were requested, so what of X comes late (a wide X, the
     // wavefronts that start last) would queue behind everyone's chunks, and nothing is computed before all of X is there.  us, chunks
     // first / X first: two, 5120 x 5120 at 30 %, 8-bit 6.56 / 6.21, 2048 x 8192 at 40 %, 8-bit 8.15 / 7.77, 16384 x 1024 at 30 % 4.95 / 4.62;
@@ -952,7 +957,7 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
             for (uint32_t u = 0; u < U; ++u) put(min(idx + u * nt, ntot - 1u), t[u]);
         }
     }
-    if constexpr (DIRECT && NB > 1) __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): nothing is left on its way
+    if constexpr (DIRECT && NB > 1) __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0)
     // all of x if it is not 16-byte aligned or its rows are longer than the NB values this launch takes
     if (NB > 1 && NB < 8 && ld != NB) {
         // one load of NB values per row of X where the alignment allows it (ld counts values of VW bytes)
