@@ -921,14 +921,17 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
         if constexpr (!residual_late) rs.prologue(c, hdr, dealt);
     };
     ECS_STAMP(c, 1);            // panel header here
-    if constexpr (!X_FIRST) request_first();
-    ECS_STAMP(c, 2);            // first chunks of every set requested
+    if constexpr (!X_FIRST) {
+        request_first();
+        ECS_STAMP(c, 2);        // first chunks of every set requested
+    }
 
 #ifdef ECS_TRACE
-    // (only meaningful for the residual-only kernel with one buffer: its three chunk loads stay in flight)
-    if (c.tr.sel == 21u) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+    // (only meaningful for residual-only kernels: the loads of their first chunks, where those are requested, stay in flight)
+    constexpr int in_flight = X_FIRST ? 0 : (TM == 0 && BATCH ? DR0B : DR) * ((DB == 16 ? 2 : 1) + VW);
+    if (c.tr.sel == 21u) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(in_flight) : "memory");
 #endif
-    ECS_STAMP(c, 21);           // this wavefront's first piece here
+    ECS_STAMP(c, 21);           // this wavefront's pieces here
     // tables and x into LDS
     // (no branches here either: with a store under a branch the compiler moves the load down to it and waits for
     // it there)
@@ -984,8 +987,11 @@ __global__ __launch_bounds__(1024) void ecspmv_kernel(const uint32_t count, cons
     } else if (!x_fast) {
         for (uint32_t i = tid; i < n; i += nt) xs[i] = x[i];
     }
-    if constexpr (X_FIRST) request_first();
     ECS_STAMP(c, 3);            // this wavefront's pieces of the tables and x written to LDS
+    if constexpr (X_FIRST) {
+        request_first();
+        ECS_STAMP(c, 2);        // first chunks of every set requested
+    }
     __syncthreads();
     ECS_STAMP(c, 4);            // first barrier passed
 

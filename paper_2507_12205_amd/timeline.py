@@ -8,6 +8,9 @@ wavefront), averaged over the traced launches, plus the gap from a launch's last
 
     python -m paper_2507_12205_amd.timeline --config 3 --shape 0 --delta-bits 4 [--json out.json]
 
+Points come in the order of a launch that requests its first chunks before x is in LDS; where x comes first (a wide x and panels of many
+chunks, no block sets) "first chunks requested" follows "tables and x pieces written to LDS".
+
 The stamped kernel is a few per cent slower than the product kernel (the stamps wait for outstanding loads where the
 product kernel would not); the event-timed figure of the same launches is printed beside it.
 """
@@ -32,7 +35,7 @@ STAMPS = [
     (20, "header and first pieces requested"),
     (1, "panel header here"),
     (2, "first chunks requested"),
-    (21, "first piece of tables / x here"),
+    (21, "pieces of tables / x here"),
     (3, "tables and x pieces written to LDS"),
     (4, "first barrier passed"),
     (5, "chunk 0 data here"),

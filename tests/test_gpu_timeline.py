@@ -46,6 +46,23 @@ def test_timeline_runs_and_points_come_in_order(tmp_path):
     assert 500.0 < d["stamp_clock_mhz"] < 3000.0
 
 
+@pytest.mark.gpu
+def test_points_where_x_comes_first(tmp_path):
+    """A wide x and no block sets: the first chunks are requested once this wavefront's pieces are in LDS (times from the start of the
+    wavefronts that passed a point, in the launches that stamped it).  Between the header and that point lie the stores of 16 wavefronts
+    x 2 KB, 0.11 us of an LDS that takes 128 bytes a cycle at 2.3 GHz, half of it for the median wavefront; where nothing lies
+    between two points they are 0.01-0.02 us apart."""
+    out = tmp_path / "t.json"
+    r = subprocess.run([sys.executable, "-m", "paper_2507_12205_amd.timeline", "--config", "2", "--shape", "1", "--delta-bits", "8",
+                        "--max-granularity", "1", "--copies", "2", "--launches", "8", "--json", str(out)],
+                       cwd=ROOT, env={k: v for k, v in os.environ.items() if k != "ECSPMV_LIB"}, capture_output=True, text=True, timeout=240)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+    by = {row["stamp"]: row for row in json.loads(out.read_text())["stamps"]}
+    assert_in_order(by)
+    after = {k: by[k]["median_us"] - by[k]["own_start_median_us"] for k in (1, 2, 4)}
+    assert after[2] > after[1] + 0.05 and after[4] > after[2], after
+
+
 def stamps(starts, passed):
     """a launch of one workgroup per entry: clock at the start, at the point and at the end, constant-rate clock at start and end"""
     T = np.zeros((2, len(starts), 1, 8), dtype=np.int64)

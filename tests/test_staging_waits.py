@@ -15,18 +15,18 @@ ARGS = ("const uint32_t, const uint32_t, const uint8_t *, const uint16_t *, uint
         "const uint32_t, const uint32_t, const uint32_t, const uint64_t, const std::conditional_t<alone(%d), NoTable, ecs::EcsBatch>")
 
 
-@pytest.fixture(scope="module")
-def bodies(tmp_path_factory):
-    """{kernel: its code} of the kernels above, compiled alone"""
-    csrc = tmp_path_factory.mktemp("kernels") / "package" / "csrc"
+def compiled(folder, kernels, *flags):
+    """{kernel: its code} of some kernels, compiled alone"""
+    csrc = folder / "package" / "csrc"
     shutil.copytree(build.CSRC, csrc)
     text = (csrc / "kernels.hip").read_text()
     text = text[:text.index("// ---- plain CSR")].replace("namespace {\n", "namespace kernels {\n", 1)
-    text += "".join(f"template __global__ void ecspmv_kernel<{', '.join(map(str, k))}>({ARGS % k[2]});\n" for k in KERNELS) + "}\n"
+    text += "".join(f"template __global__ void ecspmv_kernel<{', '.join(map(str, k))}>({ARGS % k[2]});\n" for k in kernels) + "}\n"
     (csrc / "some.hip").write_text(text)
     out = csrc / "some.ll"
     res = subprocess.run(["hipcc", "-O3", "-std=c++17", "--offload-arch=gfx950", "-w", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-                          "-x", "hip", "--cuda-device-only", "-S", "-emit-llvm", str(csrc / "some.hip"), "-o", str(out)], capture_output=True, text=True)
+                          "-x", "hip", *flags, "--cuda-device-only", "-S", "-emit-llvm", str(csrc / "some.hip"), "-o", str(out)],
+                         capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
     found = {}
     for part in out.read_text().split("\ndefine ")[1:]:
@@ -34,6 +34,11 @@ def bodies(tmp_path_factory):
         if name:
             found[tuple(int(v) for v in re.findall(r"Li(\d+)E", name.group(1)))] = part[:part.index("\n}")]
     return found
+
+
+@pytest.fixture(scope="module")
+def bodies(tmp_path_factory):
+    return compiled(tmp_path_factory.mktemp("kernels"), KERNELS)
 
 
 def first_barriers(body):
@@ -66,3 +71,13 @@ def first_barriers(body):
 def test_loads_to_lds_are_waited_for(bodies, kernel):
     waited = first_barriers(bodies[kernel])
     assert waited and all(waited), waited
+
+
+@pytest.mark.skipif(not shutil.which("hipcc"), reason="needs the compiler")
+def test_the_stamp_behind_the_pieces(tmp_path):
+    """Clock stamps, the point where a wavefront's pieces are here: all loads have returned but those of the first chunks, where they were
+    requested before: x first, chunks first (indices and two loads of values), the same with two chunks, FP32 (four)."""
+    kernels = {(0, 8, 4, 2, 1, 2): 0, (0, 4, 0, 2, 1, 2): 3, (0, 4, 2, 2, 1, 2): 6, (0, 4, 0, 2, 1, 4): 5, (0, 4, 0, 2, 2, 2): 0}
+    found = {k: [int(v) for v in re.findall(r'asm sideeffect "s_waitcnt vmcnt\(\$0\)".*?\(i32 (\d+)\)', body)]
+             for k, body in compiled(tmp_path, kernels, "-DECS_TRACE=1").items()}
+    assert found == {k: [v] for k, v in kernels.items()}
