@@ -662,7 +662,6 @@ void extract_panel(const Rows &A, const int32_t *prow, int nrows, int max_g, int
     std::vector<int> order, seen;
     std::vector<char> unselected;
     std::vector<uint64_t> common(nw), rest(nw);
-    std::vector<uint16_t> columns(64 * (size_t)nw + 64);
 
     // Algorithm 1: multi-level aggregation (outer), multi-round extraction (inner).
     for (int level = 0; (2 << level) <= max_g; ++level) {
@@ -700,6 +699,7 @@ void extract_panel(const Rows &A, const int32_t *prow, int nrows, int max_g, int
     // Decode what is left at every level into blocks of that level's granularity, coarsest first.  Columns
     // of a level >= 1 row that no longer form a valid unit (a neighbour was lifted to a coarser block and the
     // gap now exceeds the delta range) fall back to the two rows of the level below.
+    std::vector<uint16_t> columns(levels.size() > 1 ? 64 * (size_t)nw + 64 : 0);
     for (int level = (int)levels.size() - 1; level >= 1; --level) {
         Level &L = levels[level], &below = levels[level - 1];
         PanelUnits::Set &set = out.units[level - 1];
@@ -1120,9 +1120,12 @@ void encode_panel(Values &&values, int64_t n, const int32_t *prow, int nrows, co
     int64_t scan = 0;                                     // sum of the deltas of earlier lanes in this chunk
     values.blocks_written();
     // a row's elements: columns (from `col` on; col[-1]: the column "before" the first one, whose delta counts from there: that column
-    // itself, the delta is 0) and values, and once more with the zeros that fill gaps
-    RawVector<uint16_t> columns((size_t)n + 256), filled_columns;
-    RawVector<T> row_values((size_t)n + 256), filled_values;
+    // itself, the delta is 0) and values, and once more with the zeros that fill gaps; by the longest row, not by the width
+    uint32_t longest = 0;
+    for (int r = 0; r < nrows; ++r) longest = std::max(longest, lay.rowlu[(size_t)r + 1] - lay.rowlu[(size_t)r]);
+    const size_t most = (size_t)ECS_LANE_ELEMS * longest + 256;
+    RawVector<uint16_t> columns(most), filled_columns;
+    RawVector<T> row_values(most), filled_values;
     uint32_t by_delta[4][256] = {};
     for (int r = 0; r < nrows; ++r) {
         const uint32_t l0 = lay.rowlu[(size_t)r], l1 = lay.rowlu[(size_t)r + 1];
@@ -1133,22 +1136,25 @@ void encode_panel(Values &&values, int64_t n, const int32_t *prow, int nrows, co
         int widest = 0;
         for (int64_t i = 1; i < count; ++i) widest = std::max(widest, (int)col[i] - (int)col[i - 1]);
         if (widest > max_delta) {                         // explicit zero every R_P - 1 columns (Section 6.2)
-            filled_columns.resize((size_t)n + 256), filled_values.resize((size_t)n + 256);
+            filled_columns.resize(most), filled_values.resize(most);
             uint16_t *fc = filled_columns.data() + 1;
             T *fv = filled_values.data();
             int64_t k = 0;
             for (int64_t i = 0; i < count; ++i) {
-                if (i)
-                    for (int at = col[i - 1]; (int)col[i] - at > max_delta;) at += max_delta, fc[k] = (uint16_t)at, fv[k++] = 0;
+                if (i) {
+                    int at = col[i - 1];
+                    for (const int left = (int)col[i] - max_delta; at < left;) at += max_delta, fc[k] = (uint16_t)at, fv[k++] = 0;
+                    ++by_delta[i & 3][(int)col[i] - at];
+                }
                 fc[k] = col[i], fv[k++] = val[i];
             }
             col = fc, val = fv, count = k;
+        } else if (max_delta < 256) {                     // four counters for a delta, so that the same one again does not wait for itself
+            for (int64_t i = 1; i < count; ++i) ++by_delta[i & 3][(col[i] - col[i - 1]) & 0xFF];
+        } else {
+            for (int64_t i = 1; i < count; ++i) ++lay.delta_hist[hist_bin((unsigned)(col[i] - col[i - 1]))];
         }
         col[-1] = col[0];
-        if (max_delta < 256)                              // four counters for a delta, so that the same one again does not wait for itself
-            for (int64_t i = 1; i < count; ++i) ++by_delta[i & 3][(col[i] - col[i - 1]) & 0xFF];
-        else
-            for (int64_t i = 1; i < count; ++i) ++lay.delta_hist[hist_bin((unsigned)(col[i] - col[i - 1]))];
         if ((count + ECS_LANE_ELEMS - 1) / ECS_LANE_ELEMS != l1 - l0 || lane != l0 || l1 > nlanes) {
             lay.err = -100;
             return;
@@ -1182,9 +1188,12 @@ void encode_panel(Values &&values, int64_t n, const int32_t *prow, int nrows, co
             scan += (int64_t)col[ECS_LANE_ELEMS - 1] - (int64_t)col[-1];
         }
     }
-    for (unsigned d = 0; d < 256; ++d)
-        for (int k = 0; k < 4; ++k) lay.delta_hist[hist_bin(d)] += by_delta[k][d];
-    lay.delta_hist[hist_bin((unsigned)max_delta)] -= lay.gap_pads;               // fillers are no entries
+    for (int bin = 0; bin <= 8; ++bin) {                   // hist_bin: 0, 1, 2-3, 4-7, ... 128-255
+        uint32_t sum = 0;
+        for (int k = 0; k < 4; ++k)
+            for (unsigned d = bin ? 1u << (bin - 1) : 0u; d < 1u << bin; ++d) sum += by_delta[k][d];
+        lay.delta_hist[bin] += sum;
+    }
     if (lane != nlanes || nentries != hdr[PH_NRENTRIES]) lay.err = -100;
 }
 

@@ -164,3 +164,60 @@ def test_a_build_that_runs_out_of_memory_leaves_nothing_behind():
     assert res.returncode == 0, res.stderr[-2000:]
     refused, left = res.stdout.split()
     assert refused == "True" and int(left) < 100 * 1000         # less than a hundred bytes a call
+
+
+SCRATCH = r"""
+#include <cstdlib>
+#include <new>
+#include <atomic>
+static std::atomic<long long> asked{0};
+static void *counted(size_t n) { asked += (long long)n; return (malloc)(n); }
+void *operator new(size_t n) { return counted(n); }
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
+namespace std { using ::counted; }
+#define malloc counted                                    // std::malloc as well
+#include "%s/paper_2507_12205_amd/csrc/encoder.cpp"
+#include <cstdio>
+int main()
+{
+    const int m = 2000, n = 60000;
+    std::vector<int64_t> rowptr(m + 1);
+    std::vector<int32_t> col(2 * m);
+    std::vector<uint16_t> val(2 * m, 0x3C00);
+    for (int i = 0; i < m; ++i) rowptr[i + 1] = 2 * (i + 1), col[2 * i] = i, col[2 * i + 1] = i + 1000;
+    ecs::Csr A;
+    ecs::csr_from_csr(rowptr.data(), col.data(), val.data(), m, n, A);
+    ecs::BuildParams bp;
+    bp.num_panels = m, bp.num_threads = 2;
+    ecs::Image im;
+    const long long before = asked;
+    const int e = ecs::build_image({m, n, 16, nullptr, 0, &A}, bp, im);
+    printf("%%d %%lld\n", e, (asked - before - (long long)im.bytes.size()) / m);
+}
+"""
+
+
+def test_memory_asked_for_by_a_small_panel(tmp_path):
+    """A panel of one row with two entries and 60000 columns: beside the bits of a row, 7.5 KB, held by the panel and twice more while it is cut
+    into units, only what goes by its entries, no list as long as the matrix is wide (120 KB)."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src, exe = tmp_path / "scratch.cpp", tmp_path / "scratch"
+    src.write_text(SCRATCH % root)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-mpopcnt", "-pthread", "-w", str(src), "-o", str(exe)], check=True)
+    status, per_panel = map(int, subprocess.run([str(exe)], capture_output=True, text=True, check=True, timeout=300).stdout.split())
+    assert status == 0 and per_panel < 4 * 7504 + 8192, per_panel
+
+
+@pytest.mark.parametrize("delta_bits", [4, 8, 16])
+@pytest.mark.parametrize("density", [0.002, 0.05, 0.5])
+def test_histogram_of_deltas_counts_entries(delta_bits, density):
+    """Every stored entry but a row's first, by the delta it has behind the zeros that fill its gap; rows with such zeros and without"""
+    W = np.where(np.random.default_rng(3).random((40, 3000)) < density, np.float16(1), np.float16(0))
+    W[::3, ::5] = 1                                        # gaps of five columns at most
+    A, most = E.ecspmv_build_dense(W, E.make_opts(delta_bits=delta_bits, max_granularity=1)), 2 ** delta_bits - 1
+    want = [0] * 9
+    for row in W:
+        for gap in np.diff(np.nonzero(row)[0]).tolist():
+            want[min(8, (gap - (gap - 1) // most * most).bit_length())] += 1
+    assert list(A.ecspmv_stats().delta_hist) == want
