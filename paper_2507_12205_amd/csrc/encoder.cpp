@@ -726,15 +726,6 @@ inline int hist_bin(unsigned d)
 
 // index k of an array of `bits`-wide indices: a delta with 8 or 4 bits (with 4 bits the earlier delta of a byte
 // sits in its low nibble), the column itself with 16 bits (index compression switched off)
-inline void put_delta(uint8_t *d, size_t k, int bits, uint32_t v)
-{
-    if (bits == 16)
-        reinterpret_cast<uint16_t *>(d)[k] = (uint16_t)v;
-    else if (bits == 8)
-        d[k] = (uint8_t)v;
-    else
-        d[k >> 1] = (uint8_t)((k & 1) ? ((d[k >> 1] & 0x0F) | (v << 4)) : ((d[k >> 1] & 0xF0) | v));
-}
 inline uint32_t get_delta(const uint8_t *d, size_t k, int bits)
 {
     if (bits == 16) return reinterpret_cast<const uint16_t *>(d)[k];
@@ -1043,7 +1034,8 @@ void write_unit(const Values &values, const int *rows, const uint16_t *cols, T *
         for (uint32_t f = 0; f < 4 * G; ++f) v[f / ep * 16 * ep + ep * j + f % ep] = (T)row[f % G][cols[4 * j + f / G]];
 }
 
-// The indices of a lane unit, `col` being its 16 columns and col[-1] the one before: deltas, or the columns themselves with 16 bits
+// 16 indices, `col` being their columns and col[-1] the one before: deltas, or the columns themselves with 16 bits.  Whole bytes are put
+// together and written once: what was there before is not read.
 template <int BITS>
 void write_indices(const uint16_t *col, uint8_t *d)
 {
@@ -1056,6 +1048,12 @@ void write_indices(const uint16_t *col, uint8_t *d)
     if constexpr (BITS == 4)
         for (int i = 0; i < 8; ++i) b[i] = (uint8_t)(b[2 * i] | b[2 * i + 1] << 4);
     std::memcpy(d, b, 2 * BITS);
+}
+inline void write_indices(int bits, const uint16_t *col, uint8_t *d)
+{
+    if (bits == 8) write_indices<8>(col, d);
+    else if (bits == 4) write_indices<4>(col, d);
+    else write_indices<16>(col, d);
 }
 
 // Writes a panel of `bytes` bytes to P.
@@ -1098,9 +1096,9 @@ void encode_panel(Values &&values, int64_t n, const int32_t *prow, int nrows, co
             uint16_t *ue = utab + u * (1 + g);
             ue[0] = cols[0];
             uint8_t *d = P + hdr[PH_BD_OFF + t] + (size_t)unit_db * u;
-            put_delta(d, 0, delta_bits, delta_bits == 16 ? cols[0] : 0u);
-            for (unsigned k = 1; k < ECS_UNIT_COLS; ++k)
-                put_delta(d, k, delta_bits, delta_bits == 16 ? cols[k] : (uint32_t)(cols[k] - cols[k - 1]));
+            uint16_t with_first[1 + ECS_UNIT_COLS] = {cols[0]};                     // the first column's delta is 0
+            std::memcpy(with_first + 1, cols, sizeof(uint16_t) * ECS_UNIT_COLS);
+            for (unsigned k = 0; k < ECS_UNIT_COLS; k += ECS_LANE_ELEMS) write_indices(delta_bits, with_first + 1 + k, d + lane_db * (k / ECS_LANE_ELEMS));
             T *v = (T *)(P + hdr[PH_BV_OFF + t] + 64ull * vw * g * u);
             for (uint32_t r = 0; r < g; ++r) ue[1 + r] = (uint16_t)cursor[rows[r]]++;
             if (g == 2) write_unit<2>(values, rows, cols, v);
@@ -1181,9 +1179,7 @@ void encode_panel(Values &&values, int64_t n, const int32_t *prow, int nrows, co
             uint8_t *chunk = P + hdr[PH_RD_OFF] + (size_t)hdr[PH_RV_OFF] * c;
             uint8_t *d = chunk + lane_db * l;
             T *v = (T *)(chunk + (tight ? align_up(lane_db * nl, 16) : ECS_CHUNK_DBYTES(delta_bits))) + ep * l;
-            if (delta_bits == 8) write_indices<8>(col, d);
-            else if (delta_bits == 4) write_indices<4>(col, d);
-            else write_indices<16>(col, d);
+            write_indices(delta_bits, col, d);
             for (uint32_t k = 0; k < ECS_LANE_ELEMS / ep; ++k) std::memcpy(v + step * k, val + ep * k, 16);
             scan += (int64_t)col[ECS_LANE_ELEMS - 1] - (int64_t)col[-1];
         }

@@ -1,6 +1,7 @@
 """The encoder's two ways through bits and values, 64 columns at a time where the processor has AVX-512 and one by one anywhere, write
-the same images: widths around words and vectors, dense rows, rows with empty words and gaps beyond the largest delta, both value widths,
-every delta width and granularity, several threads and one."""
+the same images, from dense rows and from CSR, whatever the memory they are written to held before: widths around words and vectors,
+dense rows, rows with empty words and gaps beyond the largest delta, both value widths, every delta width and granularity, several
+threads and one."""
 import os
 import subprocess
 
@@ -12,6 +13,15 @@ HARNESS = r"""
 #include "%s/paper_2507_12205_amd/csrc/encoder.cpp"
 #include <cstdio>
 #include <cmath>
+#include <malloc.h>
+static int from_csr(const std::vector<int64_t> &p, const std::vector<int32_t> &c, const std::vector<uint16_t> &v, int m, int n, ecs::Csr &out)
+{
+    return ecs::csr_from_csr(p.data(), c.data(), v.data(), m, n, out);
+}
+static int from_csr(const std::vector<int64_t> &p, const std::vector<int32_t> &c, const std::vector<uint32_t> &v, int m, int n, ecs::Csr &out)
+{
+    return ecs::csr_from_csr_f32(p.data(), c.data(), v.data(), m, n, out);
+}
 // a matrix of m x n: entries kept with probability `density`, `shared` columns in %% kept by all rows, columns from n / 3 on empty
 // for `hole` columns
 template <typename T> static void one(int m, int n, double density, int shared, int hole, int bits, int g, int threads)
@@ -30,18 +40,29 @@ template <typename T> static void one(int m, int n, double density, int shared, 
         }
     ecs::BuildParams bp;
     bp.delta_bits = bits, bp.max_granularity = g, bp.num_threads = threads, bp.keep_small_sets = true;
-    ecs::Image im;
-    const int e = ecs::build_image({m, n, (int)(8 * sizeof(T)), W.data(), ld, nullptr}, bp, im);
-    uint64_t h = 1469598103934665603ull;
-    if (!e)
-        for (uint8_t b : im.bytes) h = (h ^ b) * 1099511628211ull;
-    printf("%%d %%d %%d %%d %%d %%d: %%d %%zu %%016llx", (int)sizeof(T), m, n, bits, g, threads, e, im.bytes.size(), (unsigned long long)h);
-    if (!e)
-        for (auto d : im.stats.delta_hist) printf(" %%lld", (long long)d);
-    printf("\n");
+    std::vector<int64_t> rowptr{0};                       // the same as CSR
+    std::vector<int32_t> col;
+    std::vector<T> val;
+    for (int i = 0; i < m; ++i, rowptr.push_back((int64_t)col.size()))
+        for (int j = 0; j < n; ++j)
+            if (W[(size_t)i * ld + j]) col.push_back(j), val.push_back(W[(size_t)i * ld + j]);
+    ecs::Csr csr;
+    if (from_csr(rowptr, col, val, m, n, csr)) printf("refused\n");
+    for (const ecs::Csr *from : {(const ecs::Csr *)nullptr, (const ecs::Csr *)&csr}) {
+        ecs::Image im;
+        const int e = ecs::build_image({m, n, (int)(8 * sizeof(T)), from ? nullptr : W.data(), from ? 0 : ld, from}, bp, im);
+        uint64_t h = 1469598103934665603ull;
+        if (!e)
+            for (uint8_t b : im.bytes) h = (h ^ b) * 1099511628211ull;
+        printf("%%d %%d %%d %%d %%d %%d: %%d %%zu %%016llx", (int)sizeof(T), m, n, bits, g, threads, e, im.bytes.size(), (unsigned long long)h);
+        if (!e)
+            for (auto d : im.stats.delta_hist) printf(" %%lld", (long long)d);
+        printf("\n");
+    }
 }
-int main()
+int main(int, char **argv)
 {
+    mallopt(M_PERTURB, atoi(argv[1]));                    // what fresh memory holds
 #ifdef ECS_AVX512
     fprintf(stderr, "%%d\n", (int)ecs::kWide);
 #endif
@@ -65,9 +86,12 @@ def test_same_images(tmp_path):
         exe = tmp_path / name
         builds[name] = (exe, subprocess.Popen(["g++", "-O1", "-std=c++17", "-mpopcnt", "-pthread", "-w", *flags, str(src), "-o", str(exe)]))
     assert all(p.wait() == 0 for _, p in builds.values())
-    got = {name: subprocess.run([str(exe)], capture_output=True, text=True, check=True, timeout=300) for name, (exe, _) in builds.items()}
-    if got["wide"].stderr.strip() != "1":
-        pytest.skip("this processor has no AVX-512")
-    wide, plain = got["wide"].stdout.splitlines(), got["plain"].stdout.splitlines()
-    assert len(wide) == 13 * 3 * 3 * 2 + 13 * 2 * 3 * 2 + 3 and wide == plain
-    assert sum(line.split(": ")[1].startswith("0 ") for line in wide) == len(wide)
+    got = {(name, fill): subprocess.run([str(exe), str(fill)], capture_output=True, text=True, check=True, timeout=300)
+           for name, (exe, _) in builds.items() for fill in (0x55, 0xAA)}
+    lines = {k: v.stdout.splitlines() for k, v in got.items()}
+    first = lines["plain", 0x55]
+    assert len(first) == 2 * (13 * 3 * 3 * 2 + 13 * 2 * 3 * 2 + 3) and first[::2] == first[1::2]         # dense, CSR
+    assert sum(line.split(": ")[1].startswith("0 ") for line in first) == len(first)
+    assert all(v == first for v in lines.values())
+    if got["wide", 0x55].stderr.strip() != "1":
+        pytest.skip("this processor has no AVX-512: the plain way only")
