@@ -1313,10 +1313,13 @@ static int launch_b(const EcsBatch &batch, uint32_t threads, uint32_t lds_bytes,
     const uint32_t per_thread = (most + threads - 1) / threads;
     // One vector alone, FP16, residual set only: the first chunks are requested once this wavefront's part of x is in LDS, as with several
     // vectors, where a panel has more than 30 chunks and x is three pieces per thread or more, or two with 8-bit deltas or on a chip that
-    // is not full.  us with the chunks / x first: three pieces, 5120 x 20480 at 20 % 11.2 / 11.0, 2048 x 20480 at 30 % 10.4 / 10.0, 1459 x
-    // 16576 at 10 % (33 chunks) 5.72 / 5.53, 8-bit 1422 x 15104 at 20 % 7.0 / 6.4; two, 8-bit 11756 x 7936 at 20 % 11.1 / 10.8, 837 x 13696 at
-    // 30 % 7.9 / 7.4, 4-bit 1310 x 10688 at 30 % (81 panels) 6.75 / 6.40, 1086 x 11289 at 20 % (67) 5.52 / 5.35; but with 256 panels 5120 x
-    // 13824 at 30 % 10.7 / 10.6 over and over and 0.2 us slower among the seven products of a layer, 8192 x 8192 10.12 / 10.15; 6067 x 9002
+    // is not full (fewer workgroups than its 256 compute units).  us with the chunks / x first: three pieces, 5120 x 20480 at 20 % 11.2 /
+    // 11.0, 2048 x 20480 at 30 % 10.4 / 10.0, 1459 x 16576 at 10 % (33 chunks) 5.72 / 5.53, 8-bit 1422 x 15104 at 20 % 7.0 / 6.4; two, 8-bit
+    // 11756 x 7936 at 20 % 11.1 / 10.8, 837 x 13696 at 30 % 7.9 / 7.4, 4-bit 1310 x 10688 at 30 % (81 panels) 6.75 / 6.40, 1086 x 11289 at 20 %
+    // (67) 5.52 / 5.35.  Two, 4-bit and 256 panels: over and over in a graph 0-2.4 % faster as well (4096 x 8704 at 30 % 6.66 / 6.51,
+    // 8192 x 10240 12.34 / 12.03, 5120 x 13824 10.82 / 10.73, 16384 x 8500 at 10 % 9.11 / 9.11, 4608 x 14001 at 40 % 12.34 / 12.33), but the
+    // seven products of a 5120 / 13824 layer launched in turn, one of them of this kind, take 0.2 us more (51.97 / 52.17, three times, repeated
+    // within 0.1 %; in graphs six layers 0-1 % faster): a product among others is what the chunks' order is kept for there.  6067 x 9002
     // at 10 % (26 chunks) 5.33 / 5.34, 909 x 11171 (22) 4.08 / 4.19, 2305 x 6528 (13) 3.86 / 4.06; one piece 5120 x 5120 5.79 / 5.95.  With
     // block sets some gain and some lose (1090 x 8000 at 40 % 6.43 / 6.27, 3256 x 9155 at 50 % 9.14 / 9.27), FP32 values lose (4096 x 8192 at
     // 30 % 9.25 / 9.59), and so do several matrices (16 x 1024 x 4096 10.2 / 10.5).
