@@ -56,3 +56,22 @@ def chunks(stats):
     """what a wavefront takes at a time, of one image: 64 lane units, 4 units (the rule counts the last one of a panel and set in full, up
     to one more for each)"""
     return stats.units_by_g[0] / 64 + block_chunks(stats)
+
+
+# FP32, one launch, 128 threads: (columns, x so many values on from a 16-byte boundary) of its matrices.  The widest need more than four
+# pieces per thread, which is what the launch's kernel follows; the others have one, a few, or none but their tables.
+MIXED_FP32 = [(333, 0), (1200, 0), (64, 1), (8001, 0), (1021, 1), (9000, 1), (2048, 0), (16, 0)]
+MIXED_THREADS = 128
+
+
+def mixed_matrix(n, g):
+    """24 rows; every third column (every one of a narrow matrix) in all of them where blocks of g rows are asked for"""
+    rng = np.random.default_rng([n, g])
+    W = np.where(rng.random((24, n)) < 0.1, rng.standard_normal((24, n)) * 0.02, 0).astype(np.float32)
+    if g > 1:
+        W[:, ::3 if n >= 1000 else 1] = np.float32(0.0103)
+    return W
+
+
+def mixed_options(g, bits):
+    return dict(delta_bits=bits, max_granularity=g, num_panels=2, threads_per_wg=MIXED_THREADS, flags=4)          # small sets are kept

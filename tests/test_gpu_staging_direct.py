@@ -1,7 +1,8 @@
 """What four pieces per thread leave of tables and x goes straight to LDS: lists that end at, before and behind a wavefront's 64
 pieces and a round of the workgroup, tables that alone are more than the four pieces, x that is no list of pieces.  FP32 with one
-vector (FP32 sums in another order than the oracle's: test_gpu_f32.check's bounds), several vectors in both widths, column by column
-with the bits of one vector."""
+vector (FP32 sums in another order than the oracle's: test_gpu_f32.check's bounds), alone and with matrices of other widths in the
+launch, several vectors in both widths, column by column with the bits of one vector."""
+import batch_cases
 import numpy as np
 import pytest
 
@@ -36,6 +37,30 @@ def test_fp32_one_vector(E, g, bits, pieces, over):  # noqa: F811
     E.ecspmv_run_batch([A] * 3, [xd.data_ptr()] * 3, [t.data_ptr() for t in ys])
     torch.cuda.synchronize()
     assert all(np.array_equal(t.cpu().numpy(), y) for t in ys)
+
+
+@pytest.mark.parametrize("g,bits", [(g, bits) for g in (1, 2, 4) for bits in (4, 8)])
+def test_wide_and_narrow_in_one_launch(E, g, bits):  # noqa: F811
+    """Every workgroup of the launch lays out LDS by its own matrix: each result in the bounds of its own, and with the bits of a launch
+    that carries it alone.  (test_kernel_choice.py holds which kernel this is.)"""
+    import torch
+    opts = batch_cases.mixed_options(g, bits)
+    mats, xs, lone = [], [], []
+    for n, off in batch_cases.MIXED_FP32:
+        W, x = batch_cases.mixed_matrix(n, g), gen.make_vector(n, seed=n).astype(np.float32)
+        A, y = check_f32(E, W, x, f"g={g} bits={bits} {n} columns", **opts)
+        flat = torch.zeros(n + 4, dtype=torch.float32, device="cuda")
+        flat[off:off + n].copy_(torch.from_numpy(x))
+        mats.append(A), xs.append(flat), lone.append(y)
+    ys = [torch.full((y.size,), float("nan"), dtype=torch.float32, device="cuda") for y in lone]
+    for order in (range(len(mats)), reversed(range(len(mats)))):
+        order = list(order)
+        for y in ys:
+            y.fill_(float("nan"))
+        E.ecspmv_run_batch([mats[k] for k in order], [xs[k].data_ptr() + 4 * batch_cases.MIXED_FP32[k][1] for k in order],
+                           [ys[k].data_ptr() for k in order])
+        torch.cuda.synchronize()
+        assert all(np.array_equal(t.cpu().numpy().view(np.uint32), y.view(np.uint32)) for t, y in zip(ys, lone)), (g, bits, order)
 
 
 @pytest.mark.parametrize("x_offset", [0, 1])

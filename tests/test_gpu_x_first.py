@@ -1,8 +1,10 @@
 """One vector alone whose x is in LDS before the first chunks are requested: two, three, four and more pieces per thread, widths that
-leave values behind the last piece, x that is no list of pieces, both delta widths.  In the oracle's band, and with the bits of a
-launch of several matrices, which requests its chunks first."""
+leave values behind the last piece, x that is no list of pieces (in tall matrices, whose tables keep the kernel the same; in wide ones
+it is then another kernel's), both delta widths.  In the oracle's band, and with the bits of a launch of several matrices, which requests
+its chunks first.  Which kernel each case takes is held by test_kernel_choice.py."""
 import numpy as np
 import pytest
+import x_first_cases
 
 from oracle import oracle as orc
 from workloads import generators as gen
@@ -12,13 +14,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("x_offset", [0, 1])
-@pytest.mark.parametrize("bits", [4, 8])
-@pytest.mark.parametrize("m,n,panels", [(33, 9000, 2), (40, 9003, 2), (24, 17001, 1), (20, 33007, 1), (12, 40000, 1)])
-def test_x_first(E, m, n, panels, bits, x_offset):  # noqa: F811
+@pytest.mark.parametrize("m,n,density,panels,bits", list(x_first_cases.CASES))
+def test_x_first(E, m, n, density, panels, bits, x_offset):  # noqa: F811
     import torch
     print(f"[case] x first {m}x{n} bits={bits} x_offset={x_offset}", flush=True)
-    W, _ = gen.small_random(m, n, 0.3, 7)
-    A = E.ecspmv_build_dense(W, E.make_opts(delta_bits=bits, max_granularity=1, num_panels=panels))
+    W = x_first_cases.matrix(m, n, density)
+    A = E.ecspmv_build_dense(W, E.make_opts(**x_first_cases.options(panels, bits)))
     assert A.ecspmv_stats().units_by_g[0] > 64 * 30 * panels + 64 * panels
     E.device.upload(A)
     x = gen.make_vector(n, seed=n)

@@ -3,6 +3,7 @@ tables and x per thread), phases, and the widths of deltas and values."""
 import batch_cases
 import pytest
 import standin
+import x_first_cases
 
 HEAD = r"""
 import re
@@ -144,3 +145,50 @@ def test_x_first(tmp_path):
     assert [g["kernel"][2:4] for g in got] == [[4, 2], [4, 2], [4, 3], [4, 4], [4, 2], [4, 2], [4, 3], [0, 2], [0, 2], [0, 1], [1, 3], [0, 4],
                                                [0, 2]], got
     assert all(31 < g["chunks"] < 70 for g in got[:8]) and 20 < got[8]["chunks"] < 30, got
+
+
+X_FIRST_CASES = HEAD + r"""
+import x_first_cases as C
+out = []
+for m, n, density, panels, bits in arg:
+    A = upload(C.matrix(m, n, density), **C.options(panels, bits))
+    got = []
+    for offset in (0, 2):
+        A.ecspmv_run(X + offset, Y, 0)
+        got.append(kernel())
+    out.append(dict(kernels=got, tables=A.ecspmv_stats().meta_stride // 16 / fake.fake_launched(THREADS)))
+print(json.dumps(out))
+"""
+
+
+def test_x_first_cases(tmp_path):
+    """what test_gpu_x_first runs on the GPU takes the kernels it is there for, with an aligned x and with one that is not"""
+    cases = list(x_first_cases.CASES)
+    beyond = 0
+    for c, got in zip(cases, standin.run(tmp_path, X_FIRST_CASES, cases)):
+        want = [[4, k] if k else [0, 1] for k in x_first_cases.CASES[c]]
+        assert got["kernels"] == [[0, c[4], *w, 1, 2] for w in want], (c, got)
+        beyond += got["tables"] > 4
+    assert beyond == 2                                    # tables that alone are more than the four pieces
+
+
+MIXED = HEAD + r"""
+import batch_cases as C
+out = []
+for g, bits in arg:
+    mats = [upload(C.mixed_matrix(n, g), **C.mixed_options(g, bits)) for n, _ in C.MIXED_FP32]
+    B.ecspmv_run_batch(mats, [X + 4 * off for _, off in C.MIXED_FP32], [Y] * len(mats), 0)
+    out.append(dict(kernel=kernel(), pieces=[(A.ecspmv_stats().meta_stride // 16 + (n // 4 if not off else 0)) / fake.fake_launched(THREADS)
+                                             for A, (n, off) in zip(mats, C.MIXED_FP32)]))
+print(json.dumps(out))
+"""
+
+
+def test_wide_and_narrow_in_one_launch(tmp_path):
+    """the launch of test_gpu_staging_direct with matrices of unequal width takes the kernel that stages more than four pieces per thread,
+    and holds matrices with more, with a few and with one"""
+    cases = [(g, bits) for g in (1, 2, 4) for bits in (4, 8)]
+    for (g, bits), got in zip(cases, standin.run(tmp_path, MIXED, cases)):
+        assert got["kernel"] == [{1: 0, 2: 1, 4: 3}[g], bits, 1, 5, 1, 4], (g, bits, got)
+        p = got["pieces"]
+        assert sum(v > 4 for v in p) >= 2 and sum(1 < v <= 4 for v in p) >= 1 and sum(v <= 1 for v in p) >= 2, (g, bits, got)
